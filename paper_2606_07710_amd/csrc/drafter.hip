@@ -35,6 +35,7 @@ namespace {
 
 constexpr int kNormThreads = 256;
 constexpr int kMaxHalfDim = 64;
+constexpr int kPairMaxTokens = 768;
 
 struct RopeParams {
     double theta[kMaxHalfDim];   // base^(-2i/D), i < D/2, formed on the host in fp64
@@ -377,10 +378,14 @@ wf_status_t launch_drafter_catchup(const wf_decoder_layer_t &L, const void *r, i
     const uint16_t *x_last = xnb + (size_t)(n - 1) * d;
     rmsnorm_bf16<<<(n + 15) / 16 * 16, kNormThreads, 0, stream>>>(
         rb, static_cast<const uint16_t *>(L.attn_norm), L.rms_eps, xnb, d, n, xnt);
-    // A backlog of one batch: its K/V and the last token's q in one launch
-    // (they only share the normalised rows).
+    // A short backlog: its K/V and the last token's q in one launch (they
+    // only share the normalised rows).  Beyond kPairMaxTokens the K/V take
+    // the LDS-tiled kernel and q a launch of its own (whole catch-up, 4096
+    // cached rows: 256 tokens 93.5 us in one launch against 98.7, 700: 108.3
+    // against 109.2, 1024: 111.8 against 112.1 tiled and 151.5 against 135.9
+    // row-major, 2048: 147.7 against 141.2).
     bool q_ready = false;
-    if (n <= kCatchupChunk) {
+    if (n <= kPairMaxTokens) {
         const wf_status_t st = launch_prefill_and_q(
             tiled, xnt, L.w_k, L.w_v, k_cache, v_cache, n, pos, cap, d, L.n_kv_heads, x_last,
             static_cast<const uint16_t *>(L.w_q),

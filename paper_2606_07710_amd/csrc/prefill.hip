@@ -17,6 +17,9 @@
 // cache pair.  Tokens are the MFMA N dimension (blocks of 16).
 // RoPE angles are formed in fp64: at positions ~65K an fp32 angle would be
 // off by ~4e-3 rad.
+// Calls with many tokens, or many layers, run prefill_gemm.hip instead: this
+// kernel re-reads the activations for every 32 or 64 features and the
+// weights for every 64 tokens.
 #include <cmath>
 
 #include "wf_api_internal.h"
@@ -355,12 +358,12 @@ PrefillPlan plan_prefill(int n_tok, int d_in, int n_kv_heads, int head_dim, int 
     // of two pairs, so each workgroup reads its slice of the activations for
     // twice the features (the activation reads across all units halve) and
     // the grid keeps more k-slices; otherwise one pair per unit.  Measured
-    // (8B shapes): 80 tokens 14.6 -> 12.8 us, 160 21.3 -> 15.3, 1024 69 ->
-    // 43, 4096 271 -> 160; at 40 tokens two-pair units were slower (their
-    // eight k-slices add a third exchange level).  Sharing a launch with the
-    // catch-up's q projection, whose workgroups take the CUs' second slots,
-    // they pay from about 384 tokens on (catch-up: 128 tokens 97.3 against
-    // 100.2 us with one-pair units, 512 tokens 108.4 against 113.7).
+    // (8B shapes): 80 tokens 14.6 -> 12.8 us; at 40 tokens two-pair units
+    // were slower (their eight k-slices add a third exchange level).
+    // Sharing a launch with the catch-up's q projection, whose workgroups
+    // take the CUs' second slots, they pay from about 384 tokens on
+    // (catch-up: 128 tokens 97.3 against 100.2 us with one-pair units, 512
+    // tokens 108.4 against 113.7).
     const int wide_min = beside_q ? kPfWideMinTokensBesideQ : kPfWideMinTokens;
     p.ppu = (n_layers == 1 && n_tok >= wide_min && pairs % 2 == 0) ? 2 : 1;
     if (p.ppu == 2) {
@@ -419,6 +422,10 @@ wf_status_t launch_prefill(wf_dtype_t dt, const void *x, const void *w_k,
         dt = WF_BF16;
     if (x_tiled && dt != WF_BF16)
         return WF_ERR_UNSUPPORTED;
+    if (dt == WF_BF16 && prefill_gemm_takes(n_tok, d_in, n_kv_heads, head_dim, n_layers))
+        return launch_prefill_gemm(tiled, x_tiled, x, w_k, w_v, k_cache, v_cache, n_tok, start_pos,
+                                   cap, d_in, n_kv_heads, head_dim, rope_base, stream, n_layers,
+                                   x_ls, w_ls, c_ls);
     PrefillParams a{x, w_k, w_v, k_cache, v_cache, n_tok, start_pos, cap, d_in,
                     n_kv_heads, {}, nullptr, 0, 1, x_ls, w_ls, c_ls, tiled ? 1 : 0, 2, 0,
                     x_tiled ? 1 : 0};

@@ -1,0 +1,480 @@
+// prefill_gemm.hip -- KV-only prefill of many tokens (Sec. 3.4 of the WhiFlash
+// paper: the backlog of a drafter switch in one batch) as an LDS-tiled matrix
+// product with the RoPE and cache-append epilogue of the small-batch kernel:
+//
+//   K[g][p+t] = RoPE(W_k[g] x_t, p+t),   V[g][p+t] = W_v[g] x_t
+//
+// A workgroup owns PW = WF*FB/2 RoPE pairs of 16-feature blocks (block f of a
+// head and block f + head_dim/2) times WT*NB*16 tokens and the whole input
+// dimension; wave (wf, wt) owns FB feature blocks (FB/2 pairs, so both halves
+// of every rotation sit in one lane) times NB token blocks.  The input
+// dimension is walked in steps of 64: the step's W and x rows travel to an
+// NBUF-deep LDS ring with global_load_lds (whole 128-byte lines), one barrier
+// a step, NBUF-1 steps in flight.
+//
+// LDS holds a 16-row block of either operand as 2 KB.  Row-major sources:
+// row r's eight 16-byte granules at r*128, granule g at g ^ (r/2 mod 8), so
+// the 16 rows of an MFMA operand read fall in distinct banks.  Tiled sources
+// (16x32 tiles of 1 KB in operand order): the step's two tiles one after the
+// other.  Either way block b, half kk of the step is read at
+// 2048*b + a per-lane offset that depends on kk only.
+//
+// What bounds it (counters and timing variants, 1013 tokens, 8B shapes): the
+// step's copies alone take 21-23 us of the call's 24, compute alone 17; the
+// operands of the next half step are read from LDS while the current half's
+// MFMAs run (30 -> 26 us), two k groups share a step where one wave per SIMD
+// would leave its latencies bare (28 -> 26), and neither the ring's depth
+// nor row-major against tiled sources matters.
+#include <cmath>
+
+#include "wf_api_internal.h"
+#include "wf_device.h"
+#include "wf_lds_dma.h"
+
+namespace wf {
+
+namespace {
+
+constexpr int kStep = 64;                // input dims per pipeline step
+constexpr int kBlockBytes = 16 * kStep * 2;
+constexpr int kMaxHalfDim = 64;
+
+struct GemmParams {
+    const char *x, *w_k, *w_v;
+    uint16_t *k_cache, *v_cache;
+    int n_tok, start_pos, cap, d_in, head_dim;
+    int kind_pairs;                      // RoPE pairs of K (and as many of V)
+    int token_blocks;                    // workgroups along the tokens
+    int pair_blocks;                     // workgroups along the pairs
+    int units, units_per_xcd;            // layers * pair_blocks * token_blocks
+    int w_tiled, x_tiled;
+    long long x_ls, w_ls, c_ls;          // element strides between layers
+    double turns[kMaxHalfDim];           // RoPE frequencies in turns per position
+};
+
+// cos and sin of 2*pi*t.  The turn is reduced in fp64 (exact), then to the
+// nearest quarter in fp32 (exact), and the rest, at most pi/4 in size, goes
+// through the Taylor series (truncation below 3e-9).
+__device__ __forceinline__ void sincos_turns(double t, float &s, float &c) {
+    const float f = (float)(t - rint(t));
+    const float q = rintf(4.f * f);
+    const float a = fmaf(q, -0.25f, f) * 6.283185307179586f;
+    const float z = a * a;
+    const float sp = fmaf(z, fmaf(z, fmaf(z, fmaf(z, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f),
+                                  -1.f / 6.f), 0.f);
+    const float sa = fmaf(a, sp, a);
+    const float ca = fmaf(z, fmaf(z, fmaf(z, fmaf(z, fmaf(z, -1.f / 3628800.f, 1.f / 40320.f),
+                                                  -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
+    const int k = (int)q & 3;            // quarters, mod 4
+    const float ss = (k & 1) ? ca : sa, cc = (k & 1) ? sa : ca;
+    s = (k & 2) ? -ss : ss;
+    c = (k == 1 || k == 2) ? -cc : cc;
+}
+
+template <int FB, int NB, int WF, int WT, int WK, int NBUF, bool NT>
+__global__ __launch_bounds__(64 * WF * WT * WK) void prefill_gemm(GemmParams a) {
+    static_assert(FB % 2 == 0, "a wave owns whole RoPE pairs");
+    constexpr int WAVES = WF * WT * WK;
+    constexpr int HPW = 2 / WK;                          // 32-dim halves per wave and step
+    static_assert(WK == 1 || WK == 2, "a step has two halves");
+    constexpr int FBLK = FB * WF, TBLK = NB * WT;        // 16-row blocks per workgroup
+    constexpr int PW = FBLK / 2;
+    constexpr int STAGE = (FBLK + TBLK) * kBlockBytes;
+    constexpr int NLOAD = STAGE / 1024;
+    constexpr int LPW = (NLOAD + WAVES - 1) / WAVES;     // wave loads per wave and step
+    __shared__ __attribute__((aligned(1024))) char ring[NBUF][STAGE];
+
+    const int unit = (int)(blockIdx.x & 7) * a.units_per_xcd + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= a.units_per_xcd || unit >= a.units)
+        return;
+    const int tb = unit % a.token_blocks;
+    const int pb = (unit / a.token_blocks) % a.pair_blocks;
+    const int layer = unit / (a.token_blocks * a.pair_blocks);
+    const int t0 = tb * TBLK * 16;
+    const int n_pairs = 2 * a.kind_pairs;
+
+    const int wave = wave_id();
+    const int lane = threadIdx.x % kWave;
+    const int m16 = lane & 15;
+    const int c4 = lane >> 4;
+    const int wf = wave % WF, wt = (wave / WF) % WT, wk = wave / (WF * WT);
+
+    // pair p of the layer (K's pairs, then V's) -> matrix row of its low block
+    const int half_blk = a.head_dim / 32;                // pairs per head
+    auto pair_row = [&](int p) {
+        const int pk = p >= a.kind_pairs ? p - a.kind_pairs : p;
+        return (pk / half_blk) * a.head_dim + (pk % half_blk) * 16;
+    };
+
+    // ---- this wave's copies: load j fills LDS bytes [1024 j, 1024 j + 1024)
+    // of a stage; blocks [0, FBLK) are W, the rest x
+    const char *base[LPW];
+    unsigned voff[LPW];
+    int step_bytes[LPW], last_off[LPW];  // bytes per step, offset of the last step
+    const size_t ld = (size_t)a.d_in * 2;
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        const int j = min(wave + WAVES * i, NLOAD - 1);
+        const int blk = j / 2, hf = j % 2;
+        const int r = 8 * hf + lane / 8;                 // row of the block (row-major)
+        const int g = (lane & 7) ^ ((r >> 1) & 7);
+        if (blk < FBLK) {
+            const int w_f = blk / FB, fb = blk % FB;
+            const int p = min(pb * PW + w_f * (FB / 2) + fb % (FB / 2), n_pairs - 1);
+            const int row = pair_row(p) + (fb < FB / 2 ? 0 : a.head_dim / 2);
+            const char *w = (p >= a.kind_pairs ? a.w_v : a.w_k) + layer * a.w_ls * 2;
+            if (a.w_tiled) {
+                base[i] = w + (size_t)(row / 16) * (a.d_in / 32) * 1024 + hf * 1024;
+                voff[i] = lane * 16;
+                step_bytes[i] = 2048;
+                last_off[i] = (a.d_in / 32 - 2) * 1024;
+            } else {
+                base[i] = w + (size_t)row * ld;
+                voff[i] = (unsigned)(r * ld) + g * 16;
+                step_bytes[i] = kStep * 2;
+                last_off[i] = (a.d_in - kStep) * 2;
+            }
+        } else {
+            const char *x = a.x + layer * a.x_ls * 2;
+            const int tblk = t0 / 16 + blk - FBLK;
+            if (a.x_tiled) {
+                base[i] = x + (size_t)min(tblk, (a.n_tok + 15) / 16 - 1) * (a.d_in / 32) * 1024 +
+                          hf * 1024;
+                voff[i] = lane * 16;
+                step_bytes[i] = 2048;
+                last_off[i] = (a.d_in / 32 - 2) * 1024;
+            } else {
+                base[i] = x;
+                voff[i] = (unsigned)(min(tblk * 16 + r, a.n_tok - 1) * ld) + g * 16;
+                step_bytes[i] = kStep * 2;
+                last_off[i] = (a.d_in - kStep) * 2;
+            }
+        }
+    }
+    // an input dimension of 64k + 32 ends with a step over its last 64 dims,
+    // of which only the second half counts
+    const int n_steps = (a.d_in + kStep - 1) / kStep;
+    const bool half_tail = a.d_in % kStep != 0;
+    auto issue = [&](int st, int buf) __attribute__((always_inline)) {
+        const unsigned slot = lds_addr(ring[0]) + buf * STAGE;
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            const int j = min(wave + WAVES * i, NLOAD - 1);
+            const char *src = base[i] + min(st * step_bytes[i], last_off[i]);
+            if (NT && j / 2 < FBLK)
+                lds_dma16_so<true>(src, voff[i], slot + j * 1024);
+            else
+                lds_dma16_so<false>(src, voff[i], slot + j * 1024);
+        }
+    };
+
+    unsigned wo[HPW], xo[HPW];           // operand offsets of this wave's halves
+#pragma unroll
+    for (int k = 0; k < HPW; ++k) {
+        const int kk = wk * HPW + k;
+        const unsigned rm = m16 * 128 + (((4 * kk + c4) ^ (m16 >> 1)) & 7) * 16;
+        const unsigned tl = kk * 1024 + lane * 16;
+        wo[k] = (a.w_tiled ? tl : rm) + wf * FB * kBlockBytes;
+        xo[k] = (a.x_tiled ? tl : rm) + (FBLK + wt * NB) * kBlockBytes;
+    }
+
+    f32x4 acc[FB][NB];
+#pragma unroll
+    for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            acc[fb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    bf16x8 wr[2][FB], xr[2][NB];         // operands in use and those arriving
+    auto load = [&](auto set, int bufi, int k) __attribute__((always_inline)) {
+        constexpr int P = decltype(set)::value;
+        const WF_LDS(char) *sp = (const WF_LDS(char) *)ring[0] + bufi * STAGE;
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb)
+            wr[P][fb] = __builtin_bit_cast(
+                bf16x8, *(const WF_LDS(u32x4) *)(sp + wo[k] + fb * kBlockBytes));
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            xr[P][nb] = __builtin_bit_cast(
+                bf16x8, *(const WF_LDS(u32x4) *)(sp + xo[k] + nb * kBlockBytes));
+    };
+    auto mma = [&](auto set) __attribute__((always_inline)) {
+        constexpr int P = decltype(set)::value;
+#pragma unroll
+        for (int fb = 0; fb < FB; ++fb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                acc[fb][nb] = mfma16x16x32(wr[P][fb], xr[P][nb], acc[fb][nb]);
+    };
+    auto wait_later = [&](int later) __attribute__((always_inline)) {
+        if (NBUF > 4 && later >= 4)
+            wait_vmcnt<(NBUF > 4 ? 4 : 0) * LPW>();
+        else if (NBUF > 3 && later >= 3)
+            wait_vmcnt<(NBUF > 3 ? 3 : 0) * LPW>();
+        else if (NBUF > 2 && later >= 2)
+            wait_vmcnt<(NBUF > 2 ? 2 : 0) * LPW>();
+        else if (later >= 1)
+            wait_vmcnt<LPW>();
+        else
+            wait_vmcnt<0>();
+    };
+    // Step st's operands are in registers (or arriving); make step st + 1's
+    // data visible and refill st's ring buffer.
+    auto advance = [&](int st, int bufi) __attribute__((always_inline)) {
+        wait_later(min(NBUF - 2, n_steps - 2 - st));
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (st + NBUF < n_steps)
+            issue(st + NBUF, bufi);
+    };
+
+#pragma unroll
+    for (int s = 0; s < NBUF; ++s)
+        if (s < n_steps)
+            issue(s, s);
+    wait_later(min(NBUF - 1, n_steps - 1));
+    asm volatile("s_barrier" ::: "memory");
+    load(ic<0>{}, 0, 0);
+    int buf = 0;
+    auto next = [&](int b) { return b + 1 == NBUF ? 0 : b + 1; };
+    if constexpr (HPW == 2) {
+        for (int st = 0; st + 1 < n_steps; ++st) {
+            load(ic<1>{}, buf, 1);
+            mma(ic<0>{});
+            advance(st, buf);
+            buf = next(buf);
+            load(ic<0>{}, buf, 0);
+            mma(ic<1>{});
+        }
+        load(ic<1>{}, buf, 1);
+        if (!half_tail)
+            mma(ic<0>{});
+        mma(ic<1>{});
+    } else {
+        const bool skip_last = half_tail && wk == 0;
+        int st = 0;
+        for (; st + 2 < n_steps; st += 2) {
+            advance(st, buf);
+            buf = next(buf);
+            load(ic<1>{}, buf, 0);
+            mma(ic<0>{});
+            advance(st + 1, buf);
+            buf = next(buf);
+            load(ic<0>{}, buf, 0);
+            mma(ic<1>{});
+        }
+        if (st + 1 < n_steps) {
+            advance(st, buf);
+            load(ic<1>{}, next(buf), 0);
+            mma(ic<0>{});
+            if (!skip_last)
+                mma(ic<1>{});
+        } else if (!skip_last) {
+            mma(ic<0>{});
+        }
+    }
+
+    // ---- the k groups' sums meet in LDS: item (pair j, token block nb) is
+    // finished by group (j*NB + nb) mod WK, which adds the others in order
+    if constexpr (WK > 1) {
+        constexpr int ITEMS = FB / 2 * NB;
+        WF_LDS(char) *ex = (WF_LDS(char) *)ring[0];
+        constexpr int GIVEN = ITEMS - ITEMS / WK;        // items a wave hands over, at most
+        static_assert(WAVES * GIVEN * 2048 <= NBUF * STAGE, "exchange fits the ring");
+        auto slot = [&](int w, int k, int it) {          // wave w of group k, its item it
+            return ex + (w * GIVEN + it - (it + WK - 1 - k) / WK) * 2048 + lane * 16;
+        };
+        __syncthreads();
+        const int wq = wave % (WF * WT);
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (it % WK != wk) {
+                WF_LDS(f32x4) *d = (WF_LDS(f32x4) *)slot(wave, wk, it);
+                d[0] = acc[it / NB][it % NB];
+                d[64] = acc[it / NB + FB / 2][it % NB];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (it % WK == wk) {
+#pragma unroll
+                for (int o = 0; o < WK; ++o) {
+                    if (o == it % WK)
+                        continue;
+                    const WF_LDS(f32x4) *d = (const WF_LDS(f32x4) *)slot(o * WF * WT + wq, o, it);
+                    acc[it / NB][it % NB] += d[0];
+                    acc[it / NB + FB / 2][it % NB] += d[64];
+                }
+            }
+    }
+
+    // ---- RoPE (K) and the cache rows: lane (m16, c4) holds features
+    // 4*c4 + i of token m16 of every (feature block, token block)
+#pragma unroll
+    for (int j = 0; j < FB / 2; ++j) {
+        const int p = pb * PW + wf * (FB / 2) + j;
+        if (p >= n_pairs)
+            continue;
+        const bool is_k = p < a.kind_pairs;
+        const int pk = is_k ? p : p - a.kind_pairs;
+        const int g = pk / half_blk;
+        const int i0 = (pk % half_blk) * 16 + 4 * c4;    // first feature of the low half
+        uint16_t *cache = (is_k ? a.k_cache : a.v_cache) + layer * a.c_ls +
+                          (size_t)g * a.cap * a.head_dim;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            const int t = t0 + (wt * NB + nb) * 16 + m16;
+            if (t >= a.n_tok || (WK > 1 && (j * NB + nb) % WK != wk))
+                continue;
+            const int pos = a.start_pos + t;
+            f32x4 lo = acc[j][nb], hi = acc[j + FB / 2][nb];
+            if (is_k) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float s, c;
+                    sincos_turns((double)pos * a.turns[i0 + i], s, c);
+                    const float l = lo[i], h = hi[i];
+                    lo[i] = l * c - h * s;
+                    hi[i] = h * c + l * s;
+                }
+            }
+            uint16_t *row = cache + (size_t)pos * a.head_dim + i0;
+            *reinterpret_cast<u32x2 *>(row) =
+                u32x2{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
+            *reinterpret_cast<u32x2 *>(row + a.head_dim / 2) =
+                u32x2{pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3])};
+        }
+    }
+}
+
+inline int cdiv(int a, int b) { return (a + b - 1) / b; }
+
+// Tile of a call: fb x nb blocks per wave, wf x wt x wk waves, nbuf stages.
+struct GemmTile {
+    int fb, nb, wf, wt, wk, nbuf;
+    int features() const { return 16 * fb * wf; }
+    int tokens() const { return 16 * nb * wt; }
+};
+
+constexpr int kComputeUnits = 256;
+
+// The tile for a call, or false where the split-K kernel of prefill.hip is
+// the better one (us per call, head_dim 128, 8 KV heads, 4096 dims unless
+// stated; that kernel's time -> this one's).
+bool pick_tile(int n_tok, int feats, int n_layers, GemmTile &t) {
+    const int blocks16 = cdiv(n_tok, 16);
+    const long long units = (long long)n_layers * cdiv(feats, 32);
+    // All tokens in one block, many layers: the call streams W once, with
+    // the non-temporal hint, so it is bound by the HBM reads in flight.  The
+    // features per workgroup follow the tokens (x is re-read by each feature
+    // block), as long as a few workgroups per CU remain; fewer stages where
+    // many workgroups share a CU.  36 layers: 16 tokens 124 -> 92 (64
+    // features 98, 128: 103), 32: 150 -> 100 (32: 110, 128: 106), 48: 177 ->
+    // 113, 80: 258 -> 125, 128: 355 -> 155; 12 layers: 10 tokens 40 -> 34,
+    // 32: 54 -> 41; 8 layers: 16 tokens 30 -> 24, 80: 61 -> 31.  Fewer
+    // layers leave it latency-bound (4 layers: 16 tokens 17 -> 20, 32: 16 ->
+    // 21): there the input dimension has to be split over workgroups.
+    if (blocks16 <= 8) {
+        const int nb = blocks16 == 7 ? 8 : blocks16;
+        if (blocks16 == 1 && units >= 512) {
+            t = {2, 1, 1, 1, 2, units >= 4 * kComputeUnits ? 2 : 4};
+            return true;
+        }
+        if (blocks16 >= 4 && units >= 8 * kComputeUnits) {
+            t = {2, nb, 4, 1, 1, 2};
+            return true;
+        }
+        if (blocks16 >= 2 && units >= (blocks16 <= 3 ? 384 : 512)) {
+            t = {2, nb, 2, 1, 2, units >= 4 * kComputeUnits ? 2 : 4};
+            return true;
+        }
+    }
+    // Otherwise the smallest tile that still runs in one round of one
+    // workgroup per CU: each step costs its LDS traffic and a barrier, so a
+    // larger tile only pays once the smaller one needs a second round (one
+    // layer: 128 tokens 15.3 -> 13.5, 256: 19.9 -> 13.5, 512: 25.7 -> 16.2,
+    // 1013: 43.8 -> 25.1 (row-major W 62 -> 26), 2048: 78.7 -> 40.2, 4096:
+    // 154 -> 69.7, where the matrix cores run at 990 TFLOP/s; the next
+    // smaller tile 20.6, 30.6, 47.8 and 86.2 from 512 tokens on).  Up to 80
+    // tokens the split over the input dimension is as fast or faster (13.3
+    // against 13.3 at 80, 6.5 at 16).
+    if (n_tok <= 80 && n_layers == 1)
+        return false;
+    if (n_tok <= 64)
+        return false;
+    for (const GemmTile c : {GemmTile{2, 1, 2, 2, 1, 4}, GemmTile{2, 2, 2, 2, 2, 4},
+                             GemmTile{4, 2, 2, 2, 2, 3}, GemmTile{2, 4, 4, 2, 1, 3},
+                             GemmTile{4, 4, 4, 2, 1, 3}}) {
+        t = c;
+        if ((long long)n_layers * cdiv(feats, c.features()) * cdiv(n_tok, c.tokens()) <=
+            kComputeUnits)
+            break;
+    }
+    return true;
+}
+
+}  // namespace
+
+bool prefill_gemm_takes(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers) {
+    GemmTile t;
+    // (per-lane row offsets are 32-bit)
+    return d_in >= kStep && (long long)std::max(n_tok, 16) * d_in * 2 < (1LL << 31) &&
+           pick_tile(n_tok, 2 * n_kv_heads * head_dim, n_layers, t);
+}
+
+wf_status_t launch_prefill_gemm(bool w_tiled, bool x_tiled, const void *x, const void *w_k,
+                                const void *w_v, void *k_cache, void *v_cache, int n_tok,
+                                int start_pos, int cap, int d_in, int n_kv_heads, int head_dim,
+                                double rope_base, hipStream_t stream, int n_layers,
+                                long long x_ls, long long w_ls, long long c_ls) {
+    GemmTile t;
+    if (!pick_tile(n_tok, 2 * n_kv_heads * head_dim, n_layers, t))
+        return WF_ERR_UNSUPPORTED;
+    GemmParams a{};
+    a.x = static_cast<const char *>(x);
+    a.w_k = static_cast<const char *>(w_k);
+    a.w_v = static_cast<const char *>(w_v);
+    a.k_cache = static_cast<uint16_t *>(k_cache);
+    a.v_cache = static_cast<uint16_t *>(v_cache);
+    a.n_tok = n_tok;
+    a.start_pos = start_pos;
+    a.cap = cap;
+    a.d_in = d_in;
+    a.head_dim = head_dim;
+    a.kind_pairs = n_kv_heads * (head_dim / 32);
+    a.w_tiled = w_tiled;
+    a.x_tiled = x_tiled;
+    a.x_ls = x_ls;
+    a.w_ls = w_ls;
+    a.c_ls = c_ls;
+    for (int i = 0; i < head_dim / 2; ++i)
+        a.turns[i] = std::pow(rope_base, -2.0 * (double)i / (double)head_dim) / 6.283185307179586;
+    a.pair_blocks = cdiv(2 * a.kind_pairs, t.features() / 32);
+    a.token_blocks = cdiv(n_tok, t.tokens());
+    const long long units = (long long)a.pair_blocks * a.token_blocks * n_layers;
+    if (units > INT32_MAX / 8)
+        return WF_ERR_UNSUPPORTED;
+    a.units = (int)units;
+    a.units_per_xcd = cdiv(a.units, 8);
+    const dim3 grid(a.units_per_xcd * 8), block(64 * t.wf * t.wt * t.wk);
+#define WF_GEMM(FBV, NBV, WFV, WTV, WKV, NBUFV, NTV)                                          \
+    if (t.fb == FBV && t.nb == NBV && t.wf == WFV && t.wt == WTV && t.wk == WKV &&            \
+        t.nbuf == NBUFV) {                                                                    \
+        prefill_gemm<FBV, NBV, WFV, WTV, WKV, NBUFV, NTV><<<grid, block, 0, stream>>>(a);     \
+    } else
+#define WF_GEMM_STREAM(NBV)                                                                   \
+    WF_GEMM(2, NBV, 4, 1, 1, 2, true) WF_GEMM(2, NBV, 2, 1, 2, 2, true)                       \
+    WF_GEMM(2, NBV, 2, 1, 2, 4, true)
+    WF_GEMM(2, 1, 1, 1, 2, 2, true) WF_GEMM(2, 1, 1, 1, 2, 4, true)
+    WF_GEMM(2, 2, 2, 1, 2, 2, true) WF_GEMM(2, 2, 2, 1, 2, 4, true)
+    WF_GEMM(2, 3, 2, 1, 2, 2, true) WF_GEMM(2, 3, 2, 1, 2, 4, true)
+    WF_GEMM_STREAM(4) WF_GEMM_STREAM(5) WF_GEMM_STREAM(6) WF_GEMM_STREAM(8)
+    WF_GEMM(2, 1, 2, 2, 1, 4, false) WF_GEMM(2, 2, 2, 2, 2, 4, false)
+    WF_GEMM(4, 2, 2, 2, 2, 3, false) WF_GEMM(2, 4, 4, 2, 1, 3, false)
+    WF_GEMM(4, 4, 4, 2, 1, 3, false)
+    { return WF_ERR_UNSUPPORTED; }
+#undef WF_GEMM_STREAM
+#undef WF_GEMM
+    return hipGetLastError() == hipSuccess ? WF_OK : WF_ERR_HIP;
+}
+
+}  // namespace wf

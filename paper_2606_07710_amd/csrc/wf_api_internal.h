@@ -159,6 +159,15 @@ wf_status_t launch_prefill(wf_dtype_t dt, const void *x, const void *w_k,
                            long long x_ls = 0, long long w_ls = 0, long long c_ls = 0,
                            bool x_tiled = false);
 
+// The same product as an LDS-tiled kernel for many tokens or many layers
+// (prefill_gemm.hip); needs no workspace.
+bool prefill_gemm_takes(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers);
+wf_status_t launch_prefill_gemm(bool w_tiled, bool x_tiled, const void *x, const void *w_k,
+                                const void *w_v, void *k_cache, void *v_cache, int n_tok,
+                                int start_pos, int cap, int d_in, int n_kv_heads, int head_dim,
+                                double rope_base, hipStream_t stream, int n_layers,
+                                long long x_ls, long long w_ls, long long c_ls);
+
 // Streaming-read probe (probe.hip): `workgroups` workgroups of 256 threads
 // read [src, src + bytes) once; sink takes workgroups * 4 KB.
 wf_status_t launch_read_probe(const void *src, size_t bytes, void *sink, int workgroups,
