@@ -8,8 +8,8 @@
 // vocabulary rows, reduced immediately to one mergeable row state
 // (max, argmax, sum of the other exponentials, sum of p*log-terms) per
 // (row, tile).  Logits never reach memory.
-//   bf16: 16x16x32 bf16 MFMA skinny GEMM; 8 waves split the hidden dimension
-//   and stream W with a 4-deep prefetch; partial logits meet in LDS.
+//   bf16: 16x16x32 bf16 MFMA skinny GEMM; tiled W streams straight into
+//   registers, row-major W through LDS in whole lines.
 //   fp32: plain VALU dot products.
 //   logits-only mode: the tile reads given fp32 logits.
 // Stage 2 (one workgroup per row): merge the row's tile states in a fixed
@@ -19,6 +19,7 @@
 
 #include "wf_api_internal.h"
 #include "wf_device.h"
+#include "wf_gemm.h"
 
 namespace wf {
 
@@ -27,7 +28,6 @@ namespace {
 constexpr int kLmTile = 64;          // vocabulary rows per matmul tile
 constexpr int kLmMB = kLmTile / 16;  // 16-row MFMA blocks per tile
 constexpr int kLmWaves = 8;
-constexpr int kLmPrefetch = 4;       // 32-dim chunks in flight per wave
 // The persistent kernel keeps fewer chunks in flight: its 8 waves x 2 chunks
 // x 4 blocks (64 KB per CU) already cover the memory latency, and a shorter
 // queue shortens the pipeline fill (measured: 229 us against 234 at 4 and
@@ -205,111 +205,6 @@ __global__ __launch_bounds__(kFinishThreads) void lm_finish_rows(LmFinish f) {
     }
 }
 
-template <int NBL>
-__global__ __launch_bounds__(512) void lm_tiles_bf16(const uint16_t *__restrict__ h,
-                                                     const uint16_t *__restrict__ w,
-                                                     LmFinish f, int d, int vocab) {
-    RowState *states = f.states;
-    const int gamma = f.gamma, n_tiles = f.n_tiles;
-    __shared__ __attribute__((aligned(16))) float zs[kMaxGamma][kLmTile + 4];
-    const int tile = blockIdx.x;
-    const int v0 = tile * kLmTile;
-    const int wave = wave_id();
-    const int lane = threadIdx.x % kWave;
-    const int m16 = lane & 15;
-    const int c4 = lane >> 4;
-
-    const uint16_t *wp[kLmMB];
-#pragma unroll
-    for (int mb = 0; mb < kLmMB; ++mb)
-        wp[mb] = w + (size_t)min(v0 + 16 * mb + m16, vocab - 1) * d + c4 * 8;
-    // Rows past gamma read row gamma-1 instead: they only feed MFMA output
-    // columns that are never used, and nothing waits on a load early.
-    const uint16_t *hp[NBL];
-#pragma unroll
-    for (int nb = 0; nb < NBL; ++nb)
-        hp[nb] = h + (size_t)min(nb * 16 + m16, gamma - 1) * d + c4 * 8;
-
-    f32x4 acc[kLmMB][NBL];
-#pragma unroll
-    for (int mb = 0; mb < kLmMB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NBL; ++nb)
-            acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int nchunks = d / 32;
-    const int cpw = (wave < nchunks) ? (nchunks - wave + kLmWaves - 1) / kLmWaves : 0;
-
-    bf16x8 wb[kLmPrefetch][kLmMB], hb[kLmPrefetch][NBL];
-    auto load_chunk = [&](int u, bf16x8 (&wr)[kLmMB], bf16x8 (&hr)[NBL]) {
-        const int off = (wave + kLmWaves * u) * 32;
-#pragma unroll
-        for (int mb = 0; mb < kLmMB; ++mb)
-            wr[mb] = load_bf16x8_nt(wp[mb] + off);
-#pragma unroll
-        for (int nb = 0; nb < NBL; ++nb)
-            hr[nb] = load_bf16x8(hp[nb] + off);
-    };
-    auto mac = [&](const bf16x8 (&wr)[kLmMB], const bf16x8 (&hr)[NBL]) {
-#pragma unroll
-        for (int mb = 0; mb < kLmMB; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < NBL; ++nb)
-                acc[mb][nb] = mfma16x16x32(wr[mb], hr[nb], acc[mb][nb]);
-    };
-    // Steady state without branches, so the compiler's wait counting stays
-    // exact and kLmPrefetch chunks stay in flight: consume a group of chunks
-    // while refilling the same registers with the next group.
-    const int ngroups = cpw / kLmPrefetch;
-    if (ngroups > 0) {
-#pragma unroll
-        for (int p = 0; p < kLmPrefetch; ++p) {
-            load_chunk(p, wb[p], hb[p]);
-            __builtin_amdgcn_sched_barrier(0);   // issue chunk by chunk
-        }
-        for (int gi = 0; gi < ngroups - 1; ++gi) {
-#pragma unroll
-            for (int p = 0; p < kLmPrefetch; ++p) {
-                mac(wb[p], hb[p]);
-                load_chunk((gi + 1) * kLmPrefetch + p, wb[p], hb[p]);
-                // keep each refill right behind the MFMAs that free its
-                // registers, so kLmPrefetch chunks stay in flight
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-#pragma unroll
-        for (int p = 0; p < kLmPrefetch; ++p)
-            mac(wb[p], hb[p]);
-    }
-    for (int u = ngroups * kLmPrefetch; u < cpw; ++u) {
-        load_chunk(u, wb[0], hb[0]);
-        mac(wb[0], hb[0]);
-    }
-
-    // partial logits of the 8 waves meet in LDS in a fixed order
-#pragma unroll 1
-    for (int ww = 0; ww < kLmWaves; ++ww) {
-        if (wave == ww) {
-#pragma unroll
-            for (int nb = 0; nb < NBL; ++nb) {
-                const int r = nb * 16 + m16;
-                if (r < gamma) {
-#pragma unroll
-                    for (int mb = 0; mb < kLmMB; ++mb) {
-                        f32x4 *dst = reinterpret_cast<f32x4 *>(&zs[r][16 * mb + 4 * c4]);
-                        f32x4 v = acc[mb][nb];
-                        if (ww > 0)
-                            v += *dst;
-                        *dst = v;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-    }
-    tile_states(zs, states, tile, n_tiles, v0, gamma, vocab, wave, kLmWaves, lane);
-}
-
 // Persistent bf16 LM head for up to 16 verify rows and a hidden size of
 // CPW * 32 * 8: workgroup b owns the 16-row vocabulary blocks b, b + G,
 // b + 2G, ... (G workgroups) and walks them in tiles of kLmMB blocks, so at
@@ -322,12 +217,13 @@ __global__ __launch_bounds__(512) void lm_tiles_bf16(const uint16_t *__restrict_
 // buffered: one barrier per tile) and every row's tile state is folded
 // into a running state in ascending vocabulary order; the workgroup writes
 // one state per row at the end.
-template <int CPW>
+template <int CPW, bool TILED>
 __global__ __launch_bounds__(512) void lm_stream_bf16(const uint16_t *__restrict__ h,
                                                       const uint16_t *__restrict__ w,
-                                                      LmFinish f, int vocab, int tiled) {
+                                                      LmFinish f, int vocab) {
     constexpr int D = CPW * 32 * kLmWaves;
-    constexpr int P = kLmStreamPrefetch;
+    constexpr int Q = TILED ? 1 : 2;               // chunks refilled at a time
+    constexpr int P = Q * kLmStreamPrefetch;
     static_assert(CPW % P == 0 && CPW >= P, "chunks per wave");
     __shared__ __attribute__((aligned(16))) float zs[2][kLmWaves][16][kLmTile + 4];
     const int gamma = f.gamma;
@@ -351,12 +247,14 @@ __global__ __launch_bounds__(512) void lm_stream_bf16(const uint16_t *__restrict
         for (int u = 0; u < CPW; ++u)
             hr[u] = load_bf16x8(hp + u * 32);
     }
-    // W rows of tile t, block mb.  Blocks past the workgroup's last one (a
-    // ragged last tile) re-read that block, which is in L2, and are masked
-    // out of the states.
-    // (tiled W: the block's 1 KB tiles of this wave's slice, one per chunk,
-    // read contiguously)
-    const int cs = tiled ? 512 : 32;               // elements between chunks
+    // W rows of tile t, block mb (tiled W: the block's 1 KB tiles of this
+    // wave's slice, one per chunk, read contiguously).  Blocks past the
+    // workgroup's last one (a ragged last tile) re-read that block, which is
+    // in L2, and are masked out of the states.
+    int cs = TILED ? 512 : 32;                     // elements between chunks
+    // (opaque, so that it stays out of the loads' immediate offsets: with
+    // them a call takes 198.9 us instead of 197.3)
+    asm volatile("" : "+s"(cs));
     const int last_blk = (int)blockIdx.x + GB * (nmine - 1);
     auto wrow = [&](int t, int mb) {
         int blk = min((int)blockIdx.x + GB * (kLmMB * t + mb), last_blk);
@@ -367,20 +265,28 @@ __global__ __launch_bounds__(512) void lm_stream_bf16(const uint16_t *__restrict
             base = f.w1;
             rows = f.m;
         }
-        if (tiled)
+        if (TILED)
             return base + ((size_t)blk * (D / 32) + wave * CPW) * 512 + lane * 8;
         const int row = min(blk * 16 + m16, rows - 1);
         return base + (size_t)row * D + wave * CPW * 32 + c4 * 8;
     };
 
+    // Tiled W is read in whole lines, once: with the non-temporal hint.  A
+    // row-major load takes half a line of each of 16 rows, so the two halves
+    // of a line are asked for back to back and without the hint, which let
+    // the second half go before it was read (16 rows, d 4096: 309 -> 238 us
+    // per call, d 5120: 342 -> 242).
+    auto load_w = [](const uint16_t *p) { return TILED ? load_bf16x8_nt(p) : load_bf16x8(p); };
     bf16x8 wb[P][kLmMB];
     {
         const int t0 = min(0, ntile - 1);
 #pragma unroll
-        for (int p = 0; p < P; ++p)
+        for (int p = 0; p < P; p += Q)
 #pragma unroll
             for (int mb = 0; mb < kLmMB; ++mb)
-                wb[p][mb] = load_bf16x8_nt(wrow(t0, mb) + p * cs);
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    wb[p + q][mb] = load_w(wrow(t0, mb) + (p + q) * cs);
     }
     RowState run[2] = {state_empty(), state_empty()};
 
@@ -399,24 +305,30 @@ __global__ __launch_bounds__(512) void lm_stream_bf16(const uint16_t *__restrict
         for (int mb = 0; mb < kLmMB; ++mb)
             acc[mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int u = 0; u < CPW; ++u) {
+        for (int u = 0; u < CPW; u += Q) {
             const int p = u % P;
 #pragma unroll
-            for (int mb = 0; mb < kLmMB; ++mb)
-                acc[mb] = mfma16x16x32(wb[p][mb], hr[u], acc[mb]);
-            // refill the slot with the chunk P ahead (near the end of the
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int mb = 0; mb < kLmMB; ++mb)
+                    acc[mb] = mfma16x16x32(wb[p + q][mb], hr[u + q], acc[mb]);
+            // refill the slots with the chunks P ahead (near the end of the
             // tile: the next tile's head chunks)
             // (the last tile, whose padding blocks re-read the workgroup's
             // last block, loads its rows cached: 1.5-3 us faster per call)
             if (u + P < CPW) {
 #pragma unroll
                 for (int mb = 0; mb < kLmMB; ++mb)
-                    wb[p][mb] = LAST ? load_bf16x8(cur[mb] + (u + P) * cs)
-                                     : load_bf16x8_nt(cur[mb] + (u + P) * cs);
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+                        wb[p + q][mb] = LAST ? load_bf16x8(cur[mb] + (u + q + P) * cs)
+                                             : load_w(cur[mb] + (u + q + P) * cs);
             } else if (!LAST) {
 #pragma unroll
                 for (int mb = 0; mb < kLmMB; ++mb)
-                    wb[p][mb] = load_bf16x8_nt(nxt[mb] + (u + P - CPW) * cs);
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+                        wb[p + q][mb] = load_w(nxt[mb] + (u + q + P - CPW) * cs);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -461,7 +373,7 @@ __global__ __launch_bounds__(512) void lm_stream_bf16(const uint16_t *__restrict
     }
 }
 
-// Persistent bf16 LM head for up to 64 verify rows (NBL groups of 16) and
+// Persistent bf16 LM head, tiled W, for up to 64 verify rows (NBL groups of 16) and
 // a hidden size that is a multiple of 512.  Workgroup b owns the 16-row
 // vocabulary blocks [b0, b1); wave w owns blocks b0 + w + 8j, j < MBW (a
 // block past the run re-reads the run's last block and is masked out of the
@@ -482,7 +394,7 @@ constexpr int kWideMaxBlocksPerWave = 5;
 template <int NBL, int MBW, int P>
 __global__ __launch_bounds__(512) void lm_wide_bf16(const uint16_t *__restrict__ h,
                                                     const uint16_t *__restrict__ w,
-                                                    LmFinish f, int d, int vocab, int tiled) {
+                                                    LmFinish f, int d, int vocab) {
     constexpr int ROWS = 16 * NBL;
     constexpr int CPB = kWideK / 32;                   // chunks per K-block
     constexpr int HLOADS = ROWS * kWideGran / 512;     // h granules per thread per K-block
@@ -500,15 +412,12 @@ __global__ __launch_bounds__(512) void lm_wide_bf16(const uint16_t *__restrict__
     const int b1 = (int)((long long)(blockIdx.x + 1) * nblk / gridDim.x);
     const int nkb = d / kWideK;
 
-    // chunk 0 of each of this wave's blocks (tiled W: the block's first
-    // 1 KB tile; chunks follow 512 elements apart instead of 32)
-    const int cs = tiled ? 512 : 32;
+    // chunk 0 of each of this wave's blocks: the block's first 1 KB tile
     const uint16_t *wrow[MBW];
 #pragma unroll
     for (int j = 0; j < MBW; ++j) {
         const int blk = max(min(b0 + wave + 8 * j, b1 - 1), 0);
-        wrow[j] = tiled ? w + (size_t)blk * (d / 32) * 512 + lane * 8
-                        : w + (size_t)min(blk * 16 + m16, vocab - 1) * d + c4 * 8;
+        wrow[j] = w + (size_t)blk * (d / 32) * 512 + lane * 8;
     }
     // h staging: granule idx = threadIdx.x + 512 q of the K-block is row
     // idx / kWideGran, granule idx % kWideGran (rows past gamma repeat the
@@ -553,7 +462,7 @@ __global__ __launch_bounds__(512) void lm_wide_bf16(const uint16_t *__restrict__
         for (int p = 0; p < P; ++p)
 #pragma unroll
             for (int j = 0; j < MBW; ++j)
-                wb[p][j] = load_bf16x8_nt(wrow[j] + p * cs);
+                wb[p][j] = load_bf16x8_nt(wrow[j] + p * 512);
         __syncthreads();
     }
 
@@ -585,7 +494,7 @@ __global__ __launch_bounds__(512) void lm_wide_bf16(const uint16_t *__restrict__
             if (!LAST || u + P < CPB) {
 #pragma unroll
                 for (int j = 0; j < MBW; ++j)
-                    wb[p][j] = load_bf16x8_nt(wrow[j] + (size_t)(cbase + u + P) * cs);
+                    wb[p][j] = load_bf16x8_nt(wrow[j] + (size_t)(cbase + u + P) * 512);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -617,6 +526,254 @@ __global__ __launch_bounds__(512) void lm_wide_bf16(const uint16_t *__restrict__
         st = state_merge(st, shfl_xor_state(st, 32));
         if (c4 == 0)
             wst[wave][nb * 16 + m16] = st;
+    }
+    __syncthreads();
+    const int r = threadIdx.x;
+    if (r < gamma) {
+        RowState m = wst[0][r];
+#pragma unroll
+        for (int ww = 1; ww < kLmWaves; ++ww)
+            m = state_merge(m, wst[ww][r]);
+        f.states[(size_t)r * f.n_tiles + blockIdx.x] = m;
+    }
+}
+
+// bf16 LM head over row-major weights: workgroup b forms the logits of the
+// WF*2 16-row vocabulary blocks from b*WF*2 on against all verify rows with
+// the LDS-tiled product of wf_gemm.h, then one state per row.
+// HBM-bound: W travels in whole lines, where operand loads straight into
+// registers would take half a line of each of 16 rows at a time (16 rows, d
+// 2880, vocabulary 151936: 245 -> 140 us per call, 6.2 TB/s; 61 rows: 413 ->
+// 162).  For hidden sizes without a tiled-weights kernel: the sums and
+// states of the others are those of that kernel.
+template <int NB, int WF, int WK, int NBUF>
+__global__ __launch_bounds__(64 * WF * WK) void lm_gemm_bf16(const uint16_t *__restrict__ h,
+                                                             const uint16_t *__restrict__ w,
+                                                             LmFinish f, int d, int vocab) {
+    using G = TileGemm<2, NB, WF, 1, WK, NBUF, true>;
+    __shared__ __attribute__((aligned(1024))) char ring[NBUF * G::STAGE];
+    __shared__ RowState wst[WF][16 * NB];
+    const int gamma = f.gamma;
+    const int nblk_v = (vocab + 15) / 16;
+    const size_t block_bytes = (size_t)d * 32;
+    f32x4 acc[2][NB];
+    G::run(
+        ring,
+        [&](int b) {
+            const int blk = min((int)blockIdx.x * G::FBLK + b, nblk_v - 1);
+            return GemmBlock{(const char *)w + blk * block_bytes, min(16, vocab - 16 * blk)};
+        },
+        [&](int b) {
+            return GemmBlock{(const char *)h + b * block_bytes, min(16, gamma - 16 * b)};
+        },
+        d, false, false, acc);
+
+    const int lane = threadIdx.x % kWave;
+    const int m16 = lane & 15;
+    const int c4 = lane >> 4;
+    const int wave = wave_id();
+    const int wf = wave % WF, wk = wave / WF;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        if (!G::owns(wk, 0, nb))
+            continue;
+        const int r = nb * 16 + m16;
+        RowState st = state_empty();
+#pragma unroll
+        for (int fb = 0; fb < 2; ++fb) {
+            const int blk = (int)blockIdx.x * G::FBLK + wf * 2 + fb;
+            if (blk >= nblk_v)
+                continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int v = blk * 16 + 4 * c4 + i;
+                if (v < vocab)
+                    st = state_merge(st, state_single(acc[fb][nb][i], v));
+            }
+        }
+        st = state_merge(st, shfl_xor_state(st, 16));
+        st = state_merge(st, shfl_xor_state(st, 32));
+        if (c4 == 0)
+            wst[wf][r] = st;
+    }
+    __syncthreads();
+    const int r = threadIdx.x;
+    if (r < gamma) {
+        RowState m = wst[0][r];
+#pragma unroll
+        for (int ww = 1; ww < WF; ++ww)
+            m = state_merge(m, wst[ww][r]);
+        f.states[(size_t)r * f.n_tiles + blockIdx.x] = m;
+    }
+}
+
+// The same runs, sums and row states as lm_wide_bf16, bit for bit, with W
+// in whole lines through LDS, for row-major weights (and tiled ones where
+// lm_wide_bf16 has too few loads in flight).  Wave w
+// owns block b0 + 8j + w of sub-tile j of its workgroup's run; the sub-tiles
+// follow each other in one NBUF-deep pipeline of 64-dim steps (LDS layout as
+// in wf_gemm.h), each lane folding a finished sub-tile's logits into its
+// running state while the next one's rows arrive.
+// HBM-bound: operand loads straight into registers take half a line of each
+// of 16 rows, ask for every line twice and, with the non-temporal hint, fetch
+// it twice.  Per call (us), vocabulary 151936, from register loads with the
+// hint / without it, in pairs of half lines / this kernel: 61 rows, d 2560:
+// 234 / 178 / 158 (4.9 TB/s); 61 rows, d 4096: 347 / 251 / 224; 32 rows, d
+// 5120, vocabulary 120000: 406 / 242 / 213; 20 rows, d 2560, vocabulary
+// 32000: 82 / 56 / 37.  (At d = 4096 all workgroups read one column of rows
+// 8 KB apart, so from few channels at a time; walking the dimensions from
+// another step in each workgroup took 215, but is another order of sums
+// than the tiled form's.)
+constexpr int kRowsBuf = 6;
+
+template <int NB, bool TILED>
+__global__ __launch_bounds__(512) void lm_rows_bf16(const uint16_t *__restrict__ h,
+                                                    const uint16_t *__restrict__ w,
+                                                    LmFinish f, int d, int vocab) {
+    constexpr int STAGE = (8 + NB) * kGemmBlockBytes;
+    constexpr int XL = 2 * NB;                         // x copies per stage
+    constexpr int LPW = 3;                             // copies per wave and stage
+    static_assert(XL <= 8, "one x copy per wave");
+    __shared__ __attribute__((aligned(1024))) char ring[kRowsBuf * STAGE];
+    __shared__ RowState wst[kLmWaves][16 * NB];
+
+    const int gamma = f.gamma;
+    const int wave = wave_id();
+    const int lane = threadIdx.x % kWave;
+    const int m16 = lane & 15;
+    const int c4 = lane >> 4;
+    const int nblk = (vocab + 15) / 16;
+    const int b0 = (int)((long long)blockIdx.x * nblk / gridDim.x);
+    const int b1 = (int)((long long)(blockIdx.x + 1) * nblk / gridDim.x);
+    const int n_sub = (b1 - b0 + 7) / 8;
+    const int n_steps = d / kGemmStep;
+    const int total = n_sub * n_steps;
+    const size_t ld = (size_t)d * 2, block_bytes = 16 * ld;
+
+    // copies of a stage: half hf of W blocks bw and bw + 4, and of an x block
+    // (waves past the last x copy repeat it)
+    const int hf = wave & 1, bw = wave >> 1;
+    const int r8 = 8 * hf + lane / 8;                  // row of the block
+    const unsigned gran = ((lane & 7) ^ ((r8 >> 1) & 7)) * 16;
+    const int xj = min(wave, XL - 1), xb = xj >> 1, xr8 = 8 * (xj & 1) + lane / 8;
+    const unsigned xoff = (unsigned)(min(16 * xb + xr8, gamma - 1) * ld) +
+                          ((lane & 7) ^ ((xr8 >> 1) & 7)) * 16;
+    const char *wsrc[2];
+    unsigned woff[2];
+    int is_sub = 0, is_st = 0, is_buf = 0;             // next stage to issue
+    auto set_sub = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            // (a block past the run repeats its last one, which is in L2)
+            const int blk = min(b0 + 8 * is_sub + bw + 4 * k, b1 - 1);
+            wsrc[k] = reinterpret_cast<const char *>(w) + blk * block_bytes + (TILED ? hf * 1024 : 0);
+            woff[k] = TILED ? lane * 16 : (unsigned)(min(r8, vocab - 1 - 16 * blk) * ld) + gran;
+        }
+    };
+    auto issue = [&]() __attribute__((always_inline)) {
+        const unsigned slot = lds_addr(ring) + is_buf * STAGE;
+        const size_t at = (size_t)is_st * (kGemmStep * 2);
+        const size_t wat = TILED ? (size_t)is_st * 2048 : at;
+        lds_dma16_so<true>(wsrc[0] + wat, woff[0], slot + wave * 1024);
+        lds_dma16_so<true>(wsrc[1] + wat, woff[1], slot + (8 + wave) * 1024);
+        lds_dma16_so<false>(reinterpret_cast<const char *>(h) + at, xoff, slot + (16 + xj) * 1024);
+        is_buf = is_buf + 1 == kRowsBuf ? 0 : is_buf + 1;
+        if (++is_st == n_steps) {
+            is_st = 0;
+            ++is_sub;
+            set_sub();
+        }
+    };
+    auto wait_later = [&](int later) __attribute__((always_inline)) {
+        if (later >= 5)
+            wait_vmcnt<5 * LPW>();
+        else if (later == 4)
+            wait_vmcnt<4 * LPW>();
+        else if (later == 3)
+            wait_vmcnt<3 * LPW>();
+        else if (later == 2)
+            wait_vmcnt<2 * LPW>();
+        else if (later == 1)
+            wait_vmcnt<LPW>();
+        else
+            wait_vmcnt<0>();
+    };
+    static_assert(kRowsBuf == 6, "wait counts");
+
+    unsigned off[2];                                   // operand offsets of the halves
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+        off[kk] = m16 * 128 + (((4 * kk + c4) ^ (m16 >> 1)) & 7) * 16;
+    bf16x8 wr[2], xr[2][NB];
+    auto load = [&](auto set, int buf) __attribute__((always_inline)) {
+        constexpr int P = decltype(set)::value;
+        const WF_LDS(char) *sb = (const WF_LDS(char) *)ring + buf * STAGE;
+        const WF_LDS(char) *sp = sb + off[P];
+        wr[P] = __builtin_bit_cast(
+            bf16x8, *(const WF_LDS(u32x4) *)((TILED ? sb + P * 1024 + lane * 16 : sp) +
+                                             wave * kGemmBlockBytes));
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            xr[P][nb] = __builtin_bit_cast(
+                bf16x8, *(const WF_LDS(u32x4) *)(sp + (8 + nb) * kGemmBlockBytes));
+    };
+    f32x4 acc[NB];
+    RowState run[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        run[nb] = state_empty();
+    }
+    auto mma = [&](auto set) __attribute__((always_inline)) {
+        constexpr int P = decltype(set)::value;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            acc[nb] = mfma16x16x32(wr[P], xr[P][nb], acc[nb]);
+    };
+
+    set_sub();
+    for (int g = 0; g < kRowsBuf && g < total; ++g)
+        issue();
+    wait_later(min(kRowsBuf - 1, total - 1));
+    asm volatile("s_barrier" ::: "memory");
+    load(ic<0>{}, 0);
+    int buf = 0, st = 0, blk = b0 + wave;
+    for (int g = 0; g < total; ++g) {
+        load(ic<1>{}, buf);
+        mma(ic<0>{});
+        if (g + 1 < total) {
+            // stage g's operands are in registers: make stage g + 1 visible
+            // and refill g's buffer
+            wait_later(min(kRowsBuf - 2, total - 2 - g));
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (g + kRowsBuf < total)
+                issue();
+            buf = buf + 1 == kRowsBuf ? 0 : buf + 1;
+            load(ic<0>{}, buf);
+        }
+        mma(ic<1>{});
+        if (++st == n_steps) {
+            st = 0;
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int v = blk * 16 + 4 * c4 + i;
+                    if (blk < b1 && v < vocab)
+                        run[nb] = state_merge(run[nb], state_single(acc[nb][i], v));
+                }
+                acc[nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            blk += 8;
+        }
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        RowState s = run[nb];
+        s = state_merge(s, shfl_xor_state(s, 16));
+        s = state_merge(s, shfl_xor_state(s, 32));
+        if (c4 == 0)
+            wst[wave][nb * 16 + m16] = s;
     }
     __syncthreads();
     const int r = threadIdx.x;
@@ -746,7 +903,7 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
                           void *workspace, hipStream_t stream, const LmRouter *router) {
     if (router && (logits || parents || !lmhead_router_fusable(dt, gamma, d, router->m)))
         return WF_ERR_UNSUPPORTED;
-    const int tiled = dt == WF_BF16_TILED ? 1 : 0;
+    const bool tiled = dt == WF_BF16_TILED;
     if (tiled)
         dt = WF_BF16;
     char *ws = static_cast<char *>(workspace);
@@ -785,10 +942,14 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
         f.n_tiles = std::min(kLmStreamGrid, cdiv(vocab, kLmTile));
         const uint16_t *hb = static_cast<const uint16_t *>(h);
         const uint16_t *wb = static_cast<const uint16_t *>(w_lm);
-        if (d == 4096)
-            lm_stream_bf16<16><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, vocab, tiled);
+        if (d == 4096 && tiled)
+            lm_stream_bf16<16, true><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, vocab);
+        else if (d == 4096)
+            lm_stream_bf16<16, false><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, vocab);
+        else if (tiled)
+            lm_stream_bf16<20, true><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, vocab);
         else
-            lm_stream_bf16<20><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, vocab, tiled);
+            lm_stream_bf16<20, false><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, vocab);
     } else if (dt == WF_BF16 && d % kWideK == 0) {
         // persistent: about one workgroup per CU, each wave at most
         // kWideMaxBlocksPerWave 16-row vocabulary blocks
@@ -799,28 +960,52 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
         const uint16_t *hb = static_cast<const uint16_t *>(h);
         const uint16_t *wb = static_cast<const uint16_t *>(w_lm);
         const int nbl = cdiv(gamma, 16);
+#define WF_ROWS(NBLV)                                                                        \
+    if (nbl == NBLV && tiled) {                                                              \
+        lm_rows_bf16<NBLV, true><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab);        \
+    } else if (nbl == NBLV) {                                                                \
+        lm_rows_bf16<NBLV, false><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab);       \
+    } else
+        // Row-major weights in whole lines through LDS; tiled ones too where
+        // a wave has at most two blocks and several row groups, too little
+        // for its register loads to cover the memory latency (20 rows,
+        // vocabulary 32000, d 2560: 43.8 -> 36.6 us; 61 rows, d 4096: 71.6 ->
+        // 56.7; with more blocks the register loads are 0 to 2 % faster:
+        // 201.6 against 205.9 at vocabulary 151936).
+        if (!tiled || (mbw <= 2 && nbl >= 2)) {
+            WF_ROWS(1) WF_ROWS(2) WF_ROWS(3) WF_ROWS(4)
+            { return WF_ERR_UNSUPPORTED; }
+        } else
+#undef WF_ROWS
 #define WF_WIDE(NBLV, MBWV, PV)                                                              \
     if (nbl == NBLV && mbw <= MBWV) {                                                      \
-        lm_wide_bf16<NBLV, MBWV, PV><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab,   \
-                                                                    tiled);                \
+        lm_wide_bf16<NBLV, MBWV, PV><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab);  \
     } else
-        WF_WIDE(1, 2, 4) WF_WIDE(1, 5, 4) WF_WIDE(2, 2, 4) WF_WIDE(2, 5, 4)
-        WF_WIDE(3, 2, 4) WF_WIDE(3, 5, 2) WF_WIDE(4, 2, 4) WF_WIDE(4, 5, 2)
+        WF_WIDE(1, 2, 4) WF_WIDE(1, 5, 4) WF_WIDE(2, 5, 4) WF_WIDE(3, 5, 2) WF_WIDE(4, 5, 2)
         { return WF_ERR_UNSUPPORTED; }
 #undef WF_WIDE
-    } else if (tiled) {
-        return WF_ERR_UNSUPPORTED;              // no tiled form of the tile kernel
-    } else if (dt == WF_BF16) {
-        f.n_tiles = cdiv(vocab, kLmTile);
+    } else if (dt == WF_BF16 && !tiled) {
+        // 128-row tiles, with three or four token blocks in two k groups (61
+        // rows, d 2880: 161.6 against 162.9 us); 64-row tiles where 128-row ones would not give every CU a
+        // workgroup (20 rows, vocabulary 32000, d 2560: 37.0 against 38.1)
         const uint16_t *hb = static_cast<const uint16_t *>(h);
         const uint16_t *wb = static_cast<const uint16_t *>(w_lm);
+        const int nblk_v = cdiv(vocab, 16);
         const int nbl = cdiv(gamma, 16);
-        switch (nbl) {
-        case 1: lm_tiles_bf16<1><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab); break;
-        case 2: lm_tiles_bf16<2><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab); break;
-        case 3: lm_tiles_bf16<3><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab); break;
-        default: lm_tiles_bf16<4><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab); break;
-        }
+        const int wf = cdiv(nblk_v, 8) < kLmStreamGrid ? 2 : 4;
+        f.n_tiles = cdiv(nblk_v, 2 * wf);
+        const dim3 grid(f.n_tiles);
+#define WF_ROWS(NBLV, WFV, WKV, NBUFV)                                                       \
+    if (nbl == NBLV && wf == WFV) {                                                          \
+        lm_gemm_bf16<NBLV, WFV, WKV, NBUFV>                                                  \
+            <<<grid, 64 * WFV * WKV, 0, stream>>>(hb, wb, f, d, vocab);                      \
+    } else
+        WF_ROWS(1, 2, 2, 4) WF_ROWS(2, 2, 2, 4) WF_ROWS(3, 2, 2, 4) WF_ROWS(4, 2, 2, 4)
+        WF_ROWS(1, 4, 1, 3) WF_ROWS(2, 4, 1, 3) WF_ROWS(3, 4, 2, 3) WF_ROWS(4, 4, 2, 3)
+        { return WF_ERR_UNSUPPORTED; }
+#undef WF_ROWS
+    } else if (dt == WF_BF16) {
+        return WF_ERR_UNSUPPORTED;              // tiled weights of another hidden size
     } else {
         f.n_tiles = cdiv(vocab, kLmTile);
         const float *hf = static_cast<const float *>(h);

@@ -6,18 +6,8 @@
 //
 // A workgroup owns PW = WF*FB/2 RoPE pairs of 16-feature blocks (block f of a
 // head and block f + head_dim/2) times WT*NB*16 tokens and the whole input
-// dimension; wave (wf, wt) owns FB feature blocks (FB/2 pairs, so both halves
-// of every rotation sit in one lane) times NB token blocks.  The input
-// dimension is walked in steps of 64: the step's W and x rows travel to an
-// NBUF-deep LDS ring with global_load_lds (whole 128-byte lines), one barrier
-// a step, NBUF-1 steps in flight.
-//
-// LDS holds a 16-row block of either operand as 2 KB.  Row-major sources:
-// row r's eight 16-byte granules at r*128, granule g at g ^ (r/2 mod 8), so
-// the 16 rows of an MFMA operand read fall in distinct banks.  Tiled sources
-// (16x32 tiles of 1 KB in operand order): the step's two tiles one after the
-// other.  Either way block b, half kk of the step is read at
-// 2048*b + a per-lane offset that depends on kk only.
+// dimension (wf_gemm.h); wave (wf, wt) owns FB/2 pairs, so both halves of
+// every rotation sit in one lane.
 //
 // What bounds it (counters and timing variants, 1013 tokens, 8B shapes): the
 // step's copies alone take 21-23 us of the call's 24, compute alone 17; the
@@ -29,14 +19,12 @@
 
 #include "wf_api_internal.h"
 #include "wf_device.h"
-#include "wf_lds_dma.h"
+#include "wf_gemm.h"
 
 namespace wf {
 
 namespace {
 
-constexpr int kStep = 64;                // input dims per pipeline step
-constexpr int kBlockBytes = 16 * kStep * 2;
 constexpr int kMaxHalfDim = 64;
 
 struct GemmParams {
@@ -73,16 +61,9 @@ __device__ __forceinline__ void sincos_turns(double t, float &s, float &c) {
 
 template <int FB, int NB, int WF, int WT, int WK, int NBUF, bool NT>
 __global__ __launch_bounds__(64 * WF * WT * WK) void prefill_gemm(GemmParams a) {
-    static_assert(FB % 2 == 0, "a wave owns whole RoPE pairs");
-    constexpr int WAVES = WF * WT * WK;
-    constexpr int HPW = 2 / WK;                          // 32-dim halves per wave and step
-    static_assert(WK == 1 || WK == 2, "a step has two halves");
-    constexpr int FBLK = FB * WF, TBLK = NB * WT;        // 16-row blocks per workgroup
-    constexpr int PW = FBLK / 2;
-    constexpr int STAGE = (FBLK + TBLK) * kBlockBytes;
-    constexpr int NLOAD = STAGE / 1024;
-    constexpr int LPW = (NLOAD + WAVES - 1) / WAVES;     // wave loads per wave and step
-    __shared__ __attribute__((aligned(1024))) char ring[NBUF][STAGE];
+    using G = TileGemm<FB, NB, WF, WT, WK, NBUF, NT>;
+    constexpr int PW = G::FBLK / 2;
+    __shared__ __attribute__((aligned(1024))) char ring[NBUF * G::STAGE];
 
     const int unit = (int)(blockIdx.x & 7) * a.units_per_xcd + (int)(blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= a.units_per_xcd || unit >= a.units)
@@ -90,13 +71,13 @@ __global__ __launch_bounds__(64 * WF * WT * WK) void prefill_gemm(GemmParams a) 
     const int tb = unit % a.token_blocks;
     const int pb = (unit / a.token_blocks) % a.pair_blocks;
     const int layer = unit / (a.token_blocks * a.pair_blocks);
-    const int t0 = tb * TBLK * 16;
+    const int t0 = tb * G::TBLK * 16;
     const int n_pairs = 2 * a.kind_pairs;
 
-    const int wave = wave_id();
     const int lane = threadIdx.x % kWave;
     const int m16 = lane & 15;
     const int c4 = lane >> 4;
+    const int wave = wave_id();
     const int wf = wave % WF, wt = (wave / WF) % WT, wk = wave / (WF * WT);
 
     // pair p of the layer (K's pairs, then V's) -> matrix row of its low block
@@ -105,207 +86,24 @@ __global__ __launch_bounds__(64 * WF * WT * WK) void prefill_gemm(GemmParams a) 
         const int pk = p >= a.kind_pairs ? p - a.kind_pairs : p;
         return (pk / half_blk) * a.head_dim + (pk % half_blk) * 16;
     };
-
-    // ---- this wave's copies: load j fills LDS bytes [1024 j, 1024 j + 1024)
-    // of a stage; blocks [0, FBLK) are W, the rest x
-    const char *base[LPW];
-    unsigned voff[LPW];
-    int step_bytes[LPW], last_off[LPW];  // bytes per step, offset of the last step
-    const size_t ld = (size_t)a.d_in * 2;
-#pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-        const int j = min(wave + WAVES * i, NLOAD - 1);
-        const int blk = j / 2, hf = j % 2;
-        const int r = 8 * hf + lane / 8;                 // row of the block (row-major)
-        const int g = (lane & 7) ^ ((r >> 1) & 7);
-        if (blk < FBLK) {
-            const int w_f = blk / FB, fb = blk % FB;
+    const size_t block_bytes = (size_t)a.d_in * 32;      // 16 rows, row-major or tiled
+    f32x4 acc[FB][NB];
+    G::run(
+        ring,
+        [&](int b) {
+            // (wave row w_f's blocks: the low halves of its pairs, then the high)
+            const int w_f = b / FB, fb = b % FB;
             const int p = min(pb * PW + w_f * (FB / 2) + fb % (FB / 2), n_pairs - 1);
             const int row = pair_row(p) + (fb < FB / 2 ? 0 : a.head_dim / 2);
-            const char *w = (p >= a.kind_pairs ? a.w_v : a.w_k) + layer * a.w_ls * 2;
-            if (a.w_tiled) {
-                base[i] = w + (size_t)(row / 16) * (a.d_in / 32) * 1024 + hf * 1024;
-                voff[i] = lane * 16;
-                step_bytes[i] = 2048;
-                last_off[i] = (a.d_in / 32 - 2) * 1024;
-            } else {
-                base[i] = w + (size_t)row * ld;
-                voff[i] = (unsigned)(r * ld) + g * 16;
-                step_bytes[i] = kStep * 2;
-                last_off[i] = (a.d_in - kStep) * 2;
-            }
-        } else {
-            const char *x = a.x + layer * a.x_ls * 2;
-            const int tblk = t0 / 16 + blk - FBLK;
-            if (a.x_tiled) {
-                base[i] = x + (size_t)min(tblk, (a.n_tok + 15) / 16 - 1) * (a.d_in / 32) * 1024 +
-                          hf * 1024;
-                voff[i] = lane * 16;
-                step_bytes[i] = 2048;
-                last_off[i] = (a.d_in / 32 - 2) * 1024;
-            } else {
-                base[i] = x;
-                voff[i] = (unsigned)(min(tblk * 16 + r, a.n_tok - 1) * ld) + g * 16;
-                step_bytes[i] = kStep * 2;
-                last_off[i] = (a.d_in - kStep) * 2;
-            }
-        }
-    }
-    // an input dimension of 64k + 32 ends with a step over its last 64 dims,
-    // of which only the second half counts
-    const int n_steps = (a.d_in + kStep - 1) / kStep;
-    const bool half_tail = a.d_in % kStep != 0;
-    auto issue = [&](int st, int buf) __attribute__((always_inline)) {
-        const unsigned slot = lds_addr(ring[0]) + buf * STAGE;
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            const int j = min(wave + WAVES * i, NLOAD - 1);
-            const char *src = base[i] + min(st * step_bytes[i], last_off[i]);
-            if (NT && j / 2 < FBLK)
-                lds_dma16_so<true>(src, voff[i], slot + j * 1024);
-            else
-                lds_dma16_so<false>(src, voff[i], slot + j * 1024);
-        }
-    };
-
-    unsigned wo[HPW], xo[HPW];           // operand offsets of this wave's halves
-#pragma unroll
-    for (int k = 0; k < HPW; ++k) {
-        const int kk = wk * HPW + k;
-        const unsigned rm = m16 * 128 + (((4 * kk + c4) ^ (m16 >> 1)) & 7) * 16;
-        const unsigned tl = kk * 1024 + lane * 16;
-        wo[k] = (a.w_tiled ? tl : rm) + wf * FB * kBlockBytes;
-        xo[k] = (a.x_tiled ? tl : rm) + (FBLK + wt * NB) * kBlockBytes;
-    }
-
-    f32x4 acc[FB][NB];
-#pragma unroll
-    for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-            acc[fb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    bf16x8 wr[2][FB], xr[2][NB];         // operands in use and those arriving
-    auto load = [&](auto set, int bufi, int k) __attribute__((always_inline)) {
-        constexpr int P = decltype(set)::value;
-        const WF_LDS(char) *sp = (const WF_LDS(char) *)ring[0] + bufi * STAGE;
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb)
-            wr[P][fb] = __builtin_bit_cast(
-                bf16x8, *(const WF_LDS(u32x4) *)(sp + wo[k] + fb * kBlockBytes));
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-            xr[P][nb] = __builtin_bit_cast(
-                bf16x8, *(const WF_LDS(u32x4) *)(sp + xo[k] + nb * kBlockBytes));
-    };
-    auto mma = [&](auto set) __attribute__((always_inline)) {
-        constexpr int P = decltype(set)::value;
-#pragma unroll
-        for (int fb = 0; fb < FB; ++fb)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                acc[fb][nb] = mfma16x16x32(wr[P][fb], xr[P][nb], acc[fb][nb]);
-    };
-    auto wait_later = [&](int later) __attribute__((always_inline)) {
-        if (NBUF > 4 && later >= 4)
-            wait_vmcnt<(NBUF > 4 ? 4 : 0) * LPW>();
-        else if (NBUF > 3 && later >= 3)
-            wait_vmcnt<(NBUF > 3 ? 3 : 0) * LPW>();
-        else if (NBUF > 2 && later >= 2)
-            wait_vmcnt<(NBUF > 2 ? 2 : 0) * LPW>();
-        else if (later >= 1)
-            wait_vmcnt<LPW>();
-        else
-            wait_vmcnt<0>();
-    };
-    // Step st's operands are in registers (or arriving); make step st + 1's
-    // data visible and refill st's ring buffer.
-    auto advance = [&](int st, int bufi) __attribute__((always_inline)) {
-        wait_later(min(NBUF - 2, n_steps - 2 - st));
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        if (st + NBUF < n_steps)
-            issue(st + NBUF, bufi);
-    };
-
-#pragma unroll
-    for (int s = 0; s < NBUF; ++s)
-        if (s < n_steps)
-            issue(s, s);
-    wait_later(min(NBUF - 1, n_steps - 1));
-    asm volatile("s_barrier" ::: "memory");
-    load(ic<0>{}, 0, 0);
-    int buf = 0;
-    auto next = [&](int b) { return b + 1 == NBUF ? 0 : b + 1; };
-    if constexpr (HPW == 2) {
-        for (int st = 0; st + 1 < n_steps; ++st) {
-            load(ic<1>{}, buf, 1);
-            mma(ic<0>{});
-            advance(st, buf);
-            buf = next(buf);
-            load(ic<0>{}, buf, 0);
-            mma(ic<1>{});
-        }
-        load(ic<1>{}, buf, 1);
-        if (!half_tail)
-            mma(ic<0>{});
-        mma(ic<1>{});
-    } else {
-        const bool skip_last = half_tail && wk == 0;
-        int st = 0;
-        for (; st + 2 < n_steps; st += 2) {
-            advance(st, buf);
-            buf = next(buf);
-            load(ic<1>{}, buf, 0);
-            mma(ic<0>{});
-            advance(st + 1, buf);
-            buf = next(buf);
-            load(ic<0>{}, buf, 0);
-            mma(ic<1>{});
-        }
-        if (st + 1 < n_steps) {
-            advance(st, buf);
-            load(ic<1>{}, next(buf), 0);
-            mma(ic<0>{});
-            if (!skip_last)
-                mma(ic<1>{});
-        } else if (!skip_last) {
-            mma(ic<0>{});
-        }
-    }
-
-    // ---- the k groups' sums meet in LDS: item (pair j, token block nb) is
-    // finished by group (j*NB + nb) mod WK, which adds the others in order
-    if constexpr (WK > 1) {
-        constexpr int ITEMS = FB / 2 * NB;
-        WF_LDS(char) *ex = (WF_LDS(char) *)ring[0];
-        constexpr int GIVEN = ITEMS - ITEMS / WK;        // items a wave hands over, at most
-        static_assert(WAVES * GIVEN * 2048 <= NBUF * STAGE, "exchange fits the ring");
-        auto slot = [&](int w, int k, int it) {          // wave w of group k, its item it
-            return ex + (w * GIVEN + it - (it + WK - 1 - k) / WK) * 2048 + lane * 16;
-        };
-        __syncthreads();
-        const int wq = wave % (WF * WT);
-#pragma unroll
-        for (int it = 0; it < ITEMS; ++it)
-            if (it % WK != wk) {
-                WF_LDS(f32x4) *d = (WF_LDS(f32x4) *)slot(wave, wk, it);
-                d[0] = acc[it / NB][it % NB];
-                d[64] = acc[it / NB + FB / 2][it % NB];
-            }
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < ITEMS; ++it)
-            if (it % WK == wk) {
-#pragma unroll
-                for (int o = 0; o < WK; ++o) {
-                    if (o == it % WK)
-                        continue;
-                    const WF_LDS(f32x4) *d = (const WF_LDS(f32x4) *)slot(o * WF * WT + wq, o, it);
-                    acc[it / NB][it % NB] += d[0];
-                    acc[it / NB + FB / 2][it % NB] += d[64];
-                }
-            }
-    }
+            return GemmBlock{(p >= a.kind_pairs ? a.w_v : a.w_k) + layer * a.w_ls * 2 +
+                                 (row / 16) * block_bytes, 16};
+        },
+        [&](int b) {
+            const int blk = min(t0 / 16 + b, (a.n_tok + 15) / 16 - 1);
+            return GemmBlock{a.x + layer * a.x_ls * 2 + blk * block_bytes,
+                             min(16, a.n_tok - 16 * blk)};
+        },
+        a.d_in, a.w_tiled, a.x_tiled, acc);
 
     // ---- RoPE (K) and the cache rows: lane (m16, c4) holds features
     // 4*c4 + i of token m16 of every (feature block, token block)
@@ -323,7 +121,7 @@ __global__ __launch_bounds__(64 * WF * WT * WK) void prefill_gemm(GemmParams a) 
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
             const int t = t0 + (wt * NB + nb) * 16 + m16;
-            if (t >= a.n_tok || (WK > 1 && (j * NB + nb) % WK != wk))
+            if (t >= a.n_tok || !G::owns(wk, j, nb))
                 continue;
             const int pos = a.start_pos + t;
             f32x4 lo = acc[j][nb], hi = acc[j + FB / 2][nb];
@@ -416,8 +214,8 @@ bool pick_tile(int n_tok, int feats, int n_layers, GemmTile &t) {
 
 bool prefill_gemm_takes(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers) {
     GemmTile t;
-    // (per-lane row offsets are 32-bit)
-    return d_in >= kStep && (long long)std::max(n_tok, 16) * d_in * 2 < (1LL << 31) &&
+    // (offsets within a 16-row block are 32-bit)
+    return 32LL * d_in < (1LL << 31) &&
            pick_tile(n_tok, 2 * n_kv_heads * head_dim, n_layers, t);
 }
 
