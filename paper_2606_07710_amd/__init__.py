@@ -196,20 +196,26 @@ def tile_weights(w, stream=None) -> TiledWeight:
 
 def _weight_code(x, *ws) -> int:
     """dtype code of a call whose activations are x and weights ws."""
-    tiled = [isinstance(w, TiledWeight) for w in ws if w is not None]
-    if any(tiled):
-        if not all(tiled) or x.dtype != torch.bfloat16:
+    tiled = n = 0
+    for w in ws:
+        if w is not None:
+            n += 1
+            tiled += isinstance(w, TiledWeight)
+    if tiled:
+        if tiled != n or x.dtype != torch.bfloat16:
             raise TypeError("tiled weights: all weights tiled, bf16 activations")
         return WF_BF16_TILED
     return _dtype_code(x)
 
 
+_DTYPE_CODES = {torch.float32: WF_F32, torch.bfloat16: WF_BF16}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return WF_F32
-    if t.dtype == torch.bfloat16:
-        return WF_BF16
-    raise TypeError(f"unsupported dtype {t.dtype}; use float32 or bfloat16")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}; use float32 or bfloat16")
+    return code
 
 
 def _dev(t, name):
@@ -219,12 +225,18 @@ def _dev(t, name):
         raise ValueError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# The current device's current stream as a raw handle: torch.cuda's own
+# current_stream() builds a Stream object around it, 2.7 us of a call that
+# takes about 3 on the host besides its kernel launches.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_device = torch._C._cuda_getDevice
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    return stream.cuda_stream if stream is not None else _raw_stream(_device())
 
 
 def _check(status, what):
@@ -253,22 +265,28 @@ def alloc_workspace(nbytes: int, device) -> torch.Tensor:
                        device=device)
 
 
+def _attn_shapes(q, k_cache, v_cache, out):
+    shape = q.shape
+    gamma, hq, dh = shape
+    kshape = k_cache.shape
+    hkv, cap, dh2 = kshape
+    if dh2 != dh or v_cache.shape != kshape:
+        raise ValueError("cache shapes do not match q")
+    if out.shape != shape or out.dtype != q.dtype:
+        raise ValueError("out must match q in shape and dtype")
+    return gamma, hq, dh, hkv, cap
+
+
 def wf_verify_attn(q, k_cache, v_cache, out, ctx_len, softmax_scale=None,
                    num_splits=0, workspace=None, stream=None):
     """q [gamma][Hq][D]; k_cache, v_cache [Hkv][cap][D]; out like q."""
-    gamma, hq, dh = q.shape
-    hkv, cap, dh2 = k_cache.shape
-    if dh2 != dh or tuple(v_cache.shape) != tuple(k_cache.shape):
-        raise ValueError("cache shapes do not match q")
-    if tuple(out.shape) != tuple(q.shape) or out.dtype != q.dtype:
-        raise ValueError("out must match q in shape and dtype")
+    gamma, hq, dh, hkv, cap = _attn_shapes(q, k_cache, v_cache, out)
     code = _dtype_code(q)
     if softmax_scale is None:
         softmax_scale = dh ** -0.5
-    need = wf_verify_attn_workspace_bytes(code, gamma, ctx_len, hq, hkv, dh,
-                                          num_splits)
     if workspace is None:
-        workspace = alloc_workspace(need, q.device)
+        workspace = alloc_workspace(wf_verify_attn_workspace_bytes(
+            code, gamma, ctx_len, hq, hkv, dh, num_splits), q.device)
     st = lib.wf_verify_attn(code, _dev(q, "q"), _dev(k_cache, "k_cache"),
                             _dev(v_cache, "v_cache"), _dev(out, "out"), gamma,
                             int(ctx_len), cap, hq, hkv, dh,
@@ -284,12 +302,7 @@ def wf_verify_attn_noalloc(q, k_cache, v_cache, out, ctx_len, softmax_scale=None
     """wf_verify_attn with the library's static device scratch instead of a
     workspace: nothing is allocated (for graph capture and callers that
     cannot allocate).  Calls that overlap in time on one GPU race."""
-    gamma, hq, dh = q.shape
-    hkv, cap, dh2 = k_cache.shape
-    if dh2 != dh or tuple(v_cache.shape) != tuple(k_cache.shape):
-        raise ValueError("cache shapes do not match q")
-    if tuple(out.shape) != tuple(q.shape) or out.dtype != q.dtype:
-        raise ValueError("out must match q in shape and dtype")
+    gamma, hq, dh, hkv, cap = _attn_shapes(q, k_cache, v_cache, out)
     if softmax_scale is None:
         softmax_scale = dh ** -0.5
     st = lib.wf_verify_attn_noalloc(_dtype_code(q), _dev(q, "q"), _dev(k_cache, "k_cache"),
@@ -314,9 +327,9 @@ def wf_kv_only_prefill(x, w_k, w_v, k_cache, v_cache, start_pos, rope_base,
     n_tok, d_in = x.shape
     hkv, cap, dh = k_cache.shape
     code = _weight_code(x, w_k, w_v)
-    need = wf_kv_only_prefill_workspace_bytes(code, n_tok, d_in, hkv, dh)
-    if workspace is None and need:
-        workspace = alloc_workspace(need, x.device)
+    if workspace is None:
+        need = wf_kv_only_prefill_workspace_bytes(code, n_tok, d_in, hkv, dh)
+        workspace = alloc_workspace(need, x.device) if need else None
     st = lib.wf_kv_only_prefill(code, _dev(x, "x"), _dev(w_k, "w_k"),
                                 _dev(w_v, "w_v"), _dev(k_cache, "k_cache"),
                                 _dev(v_cache, "v_cache"), n_tok,
@@ -345,9 +358,9 @@ def wf_kv_only_prefill_layers(x, w_k, w_v, k_cache, v_cache, start_pos, rope_bas
             w_v.stride(0) != w_k.stride(0) or k_cache.shape[0] != n_layers:
         raise ValueError("layer stacks must match")
     code = _weight_code(x, w_k, w_v)
-    need = wf_kv_only_prefill_layers_workspace_bytes(code, n_tok, d_in, hkv, dh, n_layers)
-    if workspace is None and need:
-        workspace = alloc_workspace(need, x.device)
+    if workspace is None:
+        need = wf_kv_only_prefill_layers_workspace_bytes(code, n_tok, d_in, hkv, dh, n_layers)
+        workspace = alloc_workspace(need, x.device) if need else None
     st = lib.wf_kv_only_prefill_layers(
         code, _dev(x, "x"), _dev(w_k, "w_k"), _dev(w_v, "w_v"), _dev(k_cache, "k_cache"),
         _dev(v_cache, "v_cache"), n_tok, int(start_pos), cap, d_in, hkv, dh,
@@ -370,10 +383,9 @@ def wf_lmhead_accept_entropy(h, w_lm, logits, draft, tau, argmax_out,
         gamma, d = h.shape
         vocab = w_lm.shape[0]
         code = _weight_code(h, w_lm)
-    need = wf_lmhead_workspace_bytes(gamma, vocab)
-    dev = (logits if logits is not None else h).device
     if workspace is None:
-        workspace = alloc_workspace(need, dev)
+        workspace = alloc_workspace(wf_lmhead_workspace_bytes(gamma, vocab),
+                                    (logits if logits is not None else h).device)
     st = lib.wf_lmhead_accept_entropy(
         code, _dev(h, "h"), _dev(w_lm, "w_lm"), _dev(logits, "logits"),
         _dev(draft, "draft"), gamma, d, vocab, float(tau),
@@ -388,21 +400,15 @@ def wf_verify_attn_tree(q, k_cache, v_cache, out, ctx_len, tree_mask,
                         stream=None):
     """Tree verification attention: tree_mask [gamma] int64/uint64 device
     tensor (bit j of row i: row i sees block row j); else as wf_verify_attn."""
-    gamma, hq, dh = q.shape
-    hkv, cap, dh2 = k_cache.shape
-    if dh2 != dh or tuple(v_cache.shape) != tuple(k_cache.shape):
-        raise ValueError("cache shapes do not match q")
-    if tuple(out.shape) != tuple(q.shape) or out.dtype != q.dtype:
-        raise ValueError("out must match q in shape and dtype")
+    gamma, hq, dh, hkv, cap = _attn_shapes(q, k_cache, v_cache, out)
     if tree_mask.numel() != gamma or tree_mask.element_size() != 8:
         raise ValueError("tree_mask must hold gamma 64-bit words")
     code = _dtype_code(q)
     if softmax_scale is None:
         softmax_scale = dh ** -0.5
-    need = wf_verify_attn_workspace_bytes(code, gamma, ctx_len, hq, hkv, dh,
-                                          num_splits)
     if workspace is None:
-        workspace = alloc_workspace(need, q.device)
+        workspace = alloc_workspace(wf_verify_attn_workspace_bytes(
+            code, gamma, ctx_len, hq, hkv, dh, num_splits), q.device)
     st = lib.wf_verify_attn_tree(code, _dev(q, "q"), _dev(k_cache, "k_cache"),
                                  _dev(v_cache, "v_cache"), _dev(out, "out"),
                                  _dev(tree_mask, "tree_mask"), gamma,
@@ -425,9 +431,9 @@ def wf_lmhead_accept_route_neural(h, w_lm, draft, w1, b1, w2, b2, tau_neural, ar
     vocab = w_lm.shape[0]
     m = w1.shape[0]
     code = _weight_code(h, w_lm, w1)
-    need = int(lib.wf_lmhead_route_neural_workspace_bytes(code, gamma, vocab, d, m))
     if workspace is None:
-        workspace = alloc_workspace(need, h.device)
+        workspace = alloc_workspace(int(lib.wf_lmhead_route_neural_workspace_bytes(
+            code, gamma, vocab, d, m)), h.device)
     st = lib.wf_lmhead_accept_route_neural(
         code, _dev(h, "h"), _dev(w_lm, "w_lm"), _dev(draft, "draft"), gamma, d, vocab,
         _dev(w1, "w1"), _dev(b1, "b1"), _dev(w2, "w2"), _dev(b2, "b2"), m, float(tau_neural),
@@ -450,10 +456,9 @@ def wf_lmhead_accept_tree(h, w_lm, logits, tokens, parents, tau, argmax_out,
         gamma, d = h.shape
         vocab = w_lm.shape[0]
         code = _weight_code(h, w_lm)
-    need = wf_lmhead_workspace_bytes(gamma, vocab)
-    dev = (logits if logits is not None else h).device
     if workspace is None:
-        workspace = alloc_workspace(need, dev)
+        workspace = alloc_workspace(wf_lmhead_workspace_bytes(gamma, vocab),
+                                    (logits if logits is not None else h).device)
     st = lib.wf_lmhead_accept_tree(
         code, _dev(h, "h"), _dev(w_lm, "w_lm"), _dev(logits, "logits"),
         _dev(tokens, "tokens"), _dev(parents, "parents"), gamma, d, vocab,
@@ -491,9 +496,9 @@ def wf_router_neural(h, w1, b1, w2, b2, row, tau, delta_out, route_out,
     gamma, d = h.shape
     m = w1.shape[0]
     code = _dtype_code(h)
-    need = int(lib.wf_router_workspace_bytes(code, gamma, d, m))
     if workspace is None:
-        workspace = alloc_workspace(need, h.device)
+        workspace = alloc_workspace(int(lib.wf_router_workspace_bytes(code, gamma, d, m)),
+                                    h.device)
     st = lib.wf_router_neural(code, _dev(h, "h"), _dev(w1, "w1"), _dev(b1, "b1"),
                               _dev(w2, "w2"), _dev(b2, "b2"), _dev(row, "row"),
                               gamma, d, m, float(tau), _dev(delta_out, "delta_out"),
@@ -509,7 +514,7 @@ def decoder_layer(weights, n_q_heads, n_kv_heads, rms_eps, rope_base):
     head_dim = w_q.shape[0] // n_q_heads
     if w_k.shape[0] != n_kv_heads * head_dim:
         raise ValueError("w_k rows must be n_kv_heads * head_dim")
-    layer = DecoderLayer(*[_dev(weights[n], n).value for n in DECODER_WEIGHTS],
+    layer = DecoderLayer(*[_dev(weights[n], n) for n in DECODER_WEIGHTS],
                          w_q.shape[1], n_q_heads, n_kv_heads, head_dim,
                          w_gate.shape[0], float(rms_eps), float(rope_base))
     # the struct holds raw device pointers: keep the tensors alive with it
@@ -541,10 +546,9 @@ def wf_drafter_forward(layer, r, pos, k_cache, v_cache, out, workspace=None,
     """layer: DecoderLayer; r, out [n_tok][hidden]; caches [Hkv][cap][D]."""
     n_tok = r.shape[0]
     code = WF_BF16_TILED if getattr(layer, "tiled", False) else _dtype_code(r)
-    need = int(lib.wf_drafter_forward_workspace_bytes(code, ctypes.byref(layer), n_tok,
-                                                      int(pos)))
     if workspace is None:
-        workspace = alloc_workspace(need, r.device)
+        workspace = alloc_workspace(int(lib.wf_drafter_forward_workspace_bytes(
+            code, ctypes.byref(layer), n_tok, int(pos))), r.device)
     st = lib.wf_drafter_forward(code, ctypes.byref(layer), _dev(r, "r"), n_tok, int(pos),
                                 _dev(k_cache, "k_cache"), _dev(v_cache, "v_cache"),
                                 k_cache.shape[1], _dev(out, "out"),
@@ -559,10 +563,9 @@ def wf_drafter_catchup(layer, r, pos, k_cache, v_cache, out, workspace=None,
     """layer: DecoderLayer; r [n_backlog][hidden]; out [hidden]."""
     n = r.shape[0]
     code = WF_BF16_TILED if getattr(layer, "tiled", False) else _dtype_code(r)
-    need = int(lib.wf_drafter_catchup_workspace_bytes(code, ctypes.byref(layer), n,
-                                                      int(pos)))
     if workspace is None:
-        workspace = alloc_workspace(need, r.device)
+        workspace = alloc_workspace(int(lib.wf_drafter_catchup_workspace_bytes(
+            code, ctypes.byref(layer), n, int(pos))), r.device)
     st = lib.wf_drafter_catchup(code, ctypes.byref(layer), _dev(r, "r"), n, int(pos),
                                 _dev(k_cache, "k_cache"), _dev(v_cache, "v_cache"),
                                 k_cache.shape[1], _dev(out, "out"),
