@@ -771,8 +771,19 @@ __global__ __launch_bounds__(64 * KS * RG) void attn_partial_bf16(AttnParams a) 
 
 // ---------------------------------------------------------------------------
 // fp32 split-KV partial kernel (plain VALU; one wave per (split, row, head)).
+//
+// AHEAD: a block's whole K row and, where the block is whole, the first
+// 4096 / DH keys of V are asked for before the scores need them -- two memory
+// round trips per 64 keys where 16 loads at a time took nine, for 128 to 256
+// registers.  That is what a launch of at most one wave per SIMD waits for (8
+// rows, 264 keys, 8 heads of 64: kernel 11.4 -> 5.7 us; one row, 8K keys, 32
+// heads of 128: call 109 -> 81).  Larger launches cover the latency with waves,
+// which the registers would cost them (16 rows, 1K keys, 16 heads of 128: 34.9
+// us a call, 48.3 with AHEAD).  The sums run in the same order either way.
 // ---------------------------------------------------------------------------
-template <int DH>
+constexpr int kAheadMaxWaves = 1024;     // 256 CUs x 4 SIMDs
+
+template <int DH, bool AHEAD>
 __global__ __launch_bounds__(64) void attn_partial_f32(AttnParams a) {
     constexpr int E = DH / kWave;        // output dims per lane
     __shared__ float qs[DH];
@@ -801,12 +812,40 @@ __global__ __launch_bounds__(64) void attn_partial_f32(AttnParams a) {
     for (int e = 0; e < E; ++e)
         acc[e] = 0.f;
 
+    constexpr int VB = 4096 / DH;        // V keys held: 64 registers
     for (int kb = k_begin; kb < k_end; kb += kWave) {
         const int j = kb + lane;
         const int jb = j - a.ctx_len;
         const bool vis = j < k_end && (!tree || jb < 0 || ((tm >> jb) & 1ull));
+        // every key up to cnt is a cache row in range; a masked key has
+        // p = 0 and adds nothing (no branch, so the loads can be batched)
+        const int cnt = min(kWave, k_end - kb);
+        const float *vr = vbase + (size_t)kb * DH + lane;
+        float vv[VB][E];
         float sc = -INFINITY;
-        if (vis) {
+        if constexpr (AHEAD) {
+            // (a lane past the end reads the last key's row and drops the score)
+            const float *kr = kbase + (size_t)min(j, k_end - 1) * DH;
+            f32x4 kv[DH / 4];
+#pragma unroll
+            for (int c = 0; c < DH / 4; ++c)
+                kv[c] = *reinterpret_cast<const f32x4 *>(kr + 4 * c);
+            if (cnt == kWave) {
+#pragma unroll
+                for (int t = 0; t < VB; ++t)
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+                        vv[t][e] = vr[(size_t)t * DH + e * kWave];
+            }
+            float dot = 0.f;
+#pragma unroll
+            for (int c = 0; c < DH / 4; ++c)
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    dot = fmaf(qs[4 * c + u], kv[c][u], dot);
+            if (vis)
+                sc = dot;
+        } else if (vis) {
             const float *kr = kbase + (size_t)j * DH;
             float dot = 0.f;
 #pragma unroll 16
@@ -821,16 +860,23 @@ __global__ __launch_bounds__(64) void attn_partial_f32(AttnParams a) {
 #pragma unroll
         for (int e = 0; e < E; ++e)
             acc[e] *= alpha;
-        // every key up to cnt is a cache row in range; a masked key has
-        // p = 0 and adds nothing (no branch, so the loads can be batched)
-        const int cnt = min(kWave, k_end - kb);
+        int t0 = 0;
+        if (AHEAD && cnt == kWave) {
+#pragma unroll
+            for (int t = 0; t < VB; ++t) {
+                const float pt = __shfl(p, t, kWave);
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    acc[e] = fmaf(pt, vv[t][e], acc[e]);
+            }
+            t0 = VB;
+        }
 #pragma unroll 16
-        for (int tt = 0; tt < cnt; ++tt) {
-            const float pt = __shfl(p, tt, kWave);
-            const float *vr = vbase + (size_t)(kb + tt) * DH;
+        for (int t = t0; t < cnt; ++t) {
+            const float pt = __shfl(p, t, kWave);
 #pragma unroll
             for (int e = 0; e < E; ++e)
-                acc[e] = fmaf(pt, vr[lane + e * kWave], acc[e]);
+                acc[e] = fmaf(pt, vr[(size_t)t * DH + e * kWave], acc[e]);
         }
         m = mnew;
     }
@@ -1155,10 +1201,15 @@ wf_status_t launch_attn(wf_dtype_t dt, const void *q, const void *k_cache,
         a.k32 = static_cast<const float *>(k_cache);
         a.v32 = static_cast<const float *>(v_cache);
         dim3 grid(p.splits, (unsigned)pairs), block(64);
-        if (head_dim == 128)
-            attn_partial_f32<128><<<grid, block, 0, stream>>>(a);
+        const bool ahead = (long long)p.splits * pairs <= kAheadMaxWaves;
+        if (head_dim == 128 && ahead)
+            attn_partial_f32<128, true><<<grid, block, 0, stream>>>(a);
+        else if (head_dim == 128)
+            attn_partial_f32<128, false><<<grid, block, 0, stream>>>(a);
+        else if (ahead)
+            attn_partial_f32<64, true><<<grid, block, 0, stream>>>(a);
         else
-            attn_partial_f32<64><<<grid, block, 0, stream>>>(a);
+            attn_partial_f32<64, false><<<grid, block, 0, stream>>>(a);
     }
     if (hipGetLastError() != hipSuccess)
         return WF_ERR_HIP;

@@ -786,11 +786,103 @@ __global__ __launch_bounds__(512) void lm_rows_bf16(const uint16_t *__restrict__
     }
 }
 
+// fp32 LM head for up to 16 verify rows: workgroup t owns the 64-row vocabulary tile t, each of its 8
+// waves eight of the rows; a wave's lanes run along the hidden dimension, so W
+// and h are read in whole lines straight into registers, and the 64 sums of eight
+// verify rows by eight vocabulary rows meet in a halving reduction over the
+// lanes (sum v ends in lane v).  More than eight verify rows take a second
+// pass over the tile.  VEC floats a
+// load: 4 where rows are a multiple of 4 long (the entry points take 16-byte
+// aligned tensors only, so rows are aligned too), else 1.
+//
+// What bounds it at the sizes it is used for (8 rows, d 512, vocabulary 4096:
+// 8 MB) is memory latency with 64 workgroups on the chip: every load of a
+// 256-dim chunk is in flight at once, where staging W and 64 padded rows of h
+// through LDS took a round trip and 2 barriers per 128 dims and an LDS read
+// per multiply-add: kernel 18.4 -> 9.8 us there; 8 rows, d 1024, vocabulary
+// 8000: call 37.0 -> 21.4, 16 rows: 45.5 -> 35.2.  (A variant with half the sums
+// for up to 4 rows was slower: 25.5 against 17.5 us at 4 rows.)
+constexpr int kLmF32Waves = 8;
+
+template <int VEC>
+__global__ __launch_bounds__(kLmF32Waves * kWave) void lm_tiles_f32(
+    const float *__restrict__ h, const float *__restrict__ w, LmFinish f, int d, int vocab) {
+    constexpr int RV = kLmTile / kLmF32Waves;        // vocabulary rows per wave
+    constexpr int NR = 8;                            // verify rows per pass
+    constexpr int N = RV * NR;                       // sums per wave and pass
+    static_assert(N == kWave && (VEC == 1 || VEC == 4), "one sum per lane");
+    __shared__ __attribute__((aligned(16))) float zs[kMaxGamma][kLmTile + 4];
+    const int gamma = f.gamma;
+    const int v0 = blockIdx.x * kLmTile;
+    const int wave = wave_id();
+    const int lane = threadIdx.x % kWave;
+
+    const float *wp[RV];
+#pragma unroll
+    for (int j = 0; j < RV; ++j)
+        wp[j] = w + (size_t)min(v0 + RV * wave + j, vocab - 1) * d;
+#pragma unroll 1
+    for (int r0 = 0; r0 < gamma; r0 += NR) {
+        float acc[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            acc[i] = 0.f;
+        // (VEC == 4 only where d % 4 == 0: a lane's four floats are all
+        // inside the row or all outside)
+#pragma unroll 1
+        for (int c = lane * VEC; c < d; c += kWave * VEC) {
+            float wv[RV][VEC], hv[NR][VEC];
+            auto load = [&](const float *p, float (&v)[VEC]) {
+                if constexpr (VEC == 4) {
+                    const f32x4 t = *reinterpret_cast<const f32x4 *>(p);
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e)
+                        v[e] = t[e];
+                } else {
+                    v[0] = *p;
+                }
+            };
+#pragma unroll
+            for (int j = 0; j < RV; ++j)
+                load(wp[j] + c, wv[j]);
+            // rows past gamma read the last one: their sums are dropped
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+                load(h + (size_t)min(r0 + k, gamma - 1) * d + c, hv[k]);
+#pragma unroll
+            for (int k = 0; k < NR; ++k)
+#pragma unroll
+                for (int j = 0; j < RV; ++j)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e)
+                        acc[NR * j + k] = fmaf(hv[k][e], wv[j][e], acc[NR * j + k]);
+        }
+        // (the lanes whose bit `off` is set keep the upper half of the sums)
+        int off = kWave / 2;
+#pragma unroll
+        for (int n = N / 2; n >= 1; n /= 2, off /= 2) {
+            const bool up = lane & off;
+#pragma unroll
+            for (int i = 0; i < n; ++i) {
+                const float keep = up ? acc[i + n] : acc[i];
+                const float send = up ? acc[i] : acc[i + n];
+                acc[i] = keep + __shfl_xor(send, off, kWave);
+            }
+        }
+        const int r = r0 + lane % NR;
+        if (r < gamma)
+            zs[r][RV * wave + lane / NR] = acc[0];
+    }
+    __syncthreads();
+    tile_states(zs, f.states, blockIdx.x, f.n_tiles, v0, gamma, vocab, wave, kLmF32Waves, lane);
+}
+
+// fp32 LM head for more than 16 verify rows.
 // NR = verify rows per thread (rows rq, rq + 4, ...: ceil(gamma / 4) rounded
 // up to a power of two), a template parameter so the inner loop carries no
 // per-row branches.
 template <int NR>
-__global__ __launch_bounds__(256) void lm_tiles_f32(const float *__restrict__ h,
+__global__ __launch_bounds__(256) void lm_tiles_f32_many(const float *__restrict__ h,
                                                     const float *__restrict__ w,
                                                     LmFinish f, int d, int vocab) {
     RowState *states = f.states;
@@ -1010,15 +1102,18 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
         f.n_tiles = cdiv(vocab, kLmTile);
         const float *hf = static_cast<const float *>(h);
         const float *wf32 = static_cast<const float *>(w_lm);
-        const int nr = cdiv(gamma, 4);
-        if (nr <= 2)
-            lm_tiles_f32<2><<<f.n_tiles, 256, 0, stream>>>(hf, wf32, f, d, vocab);
-        else if (nr <= 4)
-            lm_tiles_f32<4><<<f.n_tiles, 256, 0, stream>>>(hf, wf32, f, d, vocab);
-        else if (nr <= 8)
-            lm_tiles_f32<8><<<f.n_tiles, 256, 0, stream>>>(hf, wf32, f, d, vocab);
+        // up to two passes over a tile; with more rows W would come from L2
+        // and beyond once per 8 rows (61 rows, d 4096, vocabulary 60000: 1276
+        // us staged in LDS, 1459 in passes; 16 rows: 588 and 383)
+        const dim3 grid(f.n_tiles);
+        if (gamma <= 16 && d % 4 == 0)
+            lm_tiles_f32<4><<<grid, kLmF32Waves * kWave, 0, stream>>>(hf, wf32, f, d, vocab);
+        else if (gamma <= 16)
+            lm_tiles_f32<1><<<grid, kLmF32Waves * kWave, 0, stream>>>(hf, wf32, f, d, vocab);
+        else if (gamma <= 32)
+            lm_tiles_f32_many<8><<<grid, 256, 0, stream>>>(hf, wf32, f, d, vocab);
         else
-            lm_tiles_f32<16><<<f.n_tiles, 256, 0, stream>>>(hf, wf32, f, d, vocab);
+            lm_tiles_f32_many<16><<<grid, 256, 0, stream>>>(hf, wf32, f, d, vocab);
     }
     lm_finish_rows<<<gamma, kFinishThreads, 0, stream>>>(f);
     if (hipGetLastError() != hipSuccess)
