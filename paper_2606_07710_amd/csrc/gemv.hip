@@ -22,6 +22,7 @@ constexpr int kGemvWaves = 8;
 constexpr int kGemvBatch = 8;          // 32-wide chunks per wave per load batch
 constexpr int kGemvTargetWorkgroups = 1024;
 constexpr int kComputeUnits = 256;
+constexpr int kShareRows = 12;         // from this many rows on workgroups share their rows of x
 
 // FB 16-feature blocks per workgroup: with many rows each workgroup reads
 // its slice of x for FB blocks at once (x would otherwise be re-read by
@@ -152,6 +153,65 @@ __global__ __launch_bounds__(kGemvWaves * kWave) void linear_partial_bf16(
             zpart[((size_t)ks * n_out + f00 + 16 * RB * pb + u) * rows + r] = z;
         }
     }
+}
+
+// y[r][f] = bf16(res[r][f] + W x[r]) for up to 11 rows: workgroup t owns
+// 16-feature block t and the whole input dimension, so the sums never leave
+// the workgroup and no slices are stored and added by a second kernel.  Loads
+// and waves as in linear_partial_bf16; the row block's other MFMA columns come
+// for free.  What it saves is the store, the read and the launch of the slices
+// (drafter layer, d 4096, 8 rows: 103.5 -> 92.8 us with K, V and q in one
+// launch, some 7 us of it theirs; 2 rows: 96.2 -> 85.7).  The rule's two ends: from 12 rows on the
+// slices' workgroups read x once per 64 features, which this one reads once
+// per 16 (d 5120, 16 rows: 120.7 us with slices, 128.3 with this kernel), and fewer than
+// 256 blocks would leave CUs idle.
+__global__ __launch_bounds__(kGemvWaves * kWave) void linear_resid_rows_bf16(
+    const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
+    const uint16_t *__restrict__ res, uint16_t *__restrict__ y, int rows, int k_in, int n_out,
+    int tiled) {
+    constexpr int BATCH = kGemvBatch;
+    __shared__ float zs[kGemvWaves][16][17];
+    const int f0 = 16 * blockIdx.x;
+    const int wave = wave_id();
+    const int lane = threadIdx.x % kWave;
+    const int m16 = lane & 15;
+    const int c4 = lane >> 4;
+    const int n_c = k_in / 32;
+    const uint16_t *wp = tiled ? w + (size_t)blockIdx.x * n_c * 512 + lane * 8
+                               : w + (size_t)(f0 + m16) * k_in + c4 * 8;
+    const int wstep = tiled ? 512 : 32;
+    // rows past `rows` read the last row: their columns are never used
+    const uint16_t *xp = x + (size_t)min(m16, rows - 1) * k_in + c4 * 8;
+
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int cb = wave; cb < n_c; cb += kGemvWaves * BATCH) {
+        bf16x8 wr[BATCH], xr[BATCH];
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int c = cb + kGemvWaves * u;
+            if (c < n_c) {
+                wr[u] = load_bf16x8_nt(wp + (size_t)c * wstep);
+                xr[u] = load_bf16x8(xp + c * 32);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+            if (cb + kGemvWaves * u < n_c)
+                acc = mfma16x16x32(wr[u], xr[u], acc);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        zs[wave][4 * c4 + i][m16] = acc[i];
+    __syncthreads();
+    const int u = threadIdx.x % 16, r = threadIdx.x / 16;
+    if (r >= rows)                       // 512 threads: r up to 31
+        return;
+    float z = zs[0][u][r];
+#pragma unroll
+    for (int ww = 1; ww < kGemvWaves; ++ww)
+        z += zs[ww][u][r];
+    const size_t at = (size_t)r * n_out + f0 + u;
+    y[at] = f32_to_bf16(z + bf16_to_f32(res[at]));
 }
 
 // Skinny linear layer with its epilogue in the same kernel, for a single
@@ -322,6 +382,16 @@ wf_status_t launch_linear_resid(const uint16_t *x, const uint16_t *w, const uint
     return hipGetLastError() == hipSuccess ? WF_OK : WF_ERR_HIP;
 }
 
+wf_status_t launch_linear_resid_rows(const uint16_t *x, const uint16_t *w, const uint16_t *res,
+                                     int rows, int k_in, int n_out, uint16_t *y,
+                                     hipStream_t stream, bool tiled) {
+    if (rows < 1 || rows >= kShareRows || n_out % 16 || k_in % 32 || n_out / 16 < kComputeUnits)
+        return WF_ERR_UNSUPPORTED;
+    linear_resid_rows_bf16<<<n_out / 16, kGemvWaves * kWave, 0, stream>>>(
+        x, w, res, y, rows, k_in, n_out, tiled ? 1 : 0);
+    return hipGetLastError() == hipSuccess ? WF_OK : WF_ERR_HIP;
+}
+
 wf_status_t launch_linear_norm_swiglu(const uint16_t *x, const uint16_t *gain, float eps,
                                       const uint16_t *w_gate, const uint16_t *w_up, int k_in,
                                       int inter, uint16_t *act, hipStream_t stream,
@@ -372,7 +442,7 @@ wf_status_t launch_linear_partial(const uint16_t *x, const uint16_t *w_a,
     // 64-token drafter layer).
     const int tiles = n_out / 16;
     int fb = 1;
-    if (rows >= 12) {
+    if (rows >= kShareRows) {
         auto cost = [&](int f) {
             return cdiv(tiles / f * ks, kComputeUnits) * (16 * f + 16 * nbl);
         };
@@ -400,7 +470,7 @@ wf_status_t launch_linear_swiglu(const uint16_t *x, const uint16_t *w_gate,
                                  uint16_t *act, hipStream_t stream, bool tiled) {
     const int tiles = 2 * inter / 16;
     const int nbl = cdiv(rows, 16);
-    if (rows < 12 || rows > 64 || inter % 16 || k_in % 32 || linear_slices(k_in, 2 * inter) != 1)
+    if (rows < kShareRows || rows > 64 || inter % 16 || k_in % 32 || linear_slices(k_in, 2 * inter) != 1)
         return WF_ERR_UNSUPPORTED;
     // the block count of the split launch's rule, among those whose gate
     // half divides the gate blocks

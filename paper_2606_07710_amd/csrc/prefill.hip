@@ -54,6 +54,7 @@ struct PrefillParams {
     int rope_shift;            // RoPE position = cache row position + rope_shift
     int x_tiled;               // x in 16-token x 32-dim tiles of 1 KB, token rows
                                // padded to a multiple of 16 (bf16 path)
+    int out_heads;             // 0: cache layout [head][cap][D]; else rows [token][out_heads][D]
 };
 
 // Rotation of the pair (lo, hi) = (k_i, k_{i+D/2}) by pos * theta_i, with
@@ -269,7 +270,8 @@ __device__ __forceinline__ void prefill_body(const PrefillParams &a, int unit, i
         float l = lo[n], h = hi[n];
         if (kind == 0)
             rope_pair(l, h, a.theta[16 * pair + e], pos + a.rope_shift);
-        uint16_t *row = cache + ((size_t)g * a.cap + pos) * DH;
+        uint16_t *row = cache + (a.out_heads ? (size_t)pos * a.out_heads + g
+                                             : (size_t)g * a.cap + pos) * DH;
         row[16 * pair + e] = f32_to_bf16(l);
         row[DH / 2 + 16 * pair + e] = f32_to_bf16(h);
     }
@@ -284,7 +286,9 @@ __global__ __launch_bounds__(256) void prefill_bf16(PrefillParams a) {
 // first problem's grid (units1 x ks1 x z1, flattened), the rest the
 // second's.  Each keeps its own exchange slots (disjoint parts of the zero
 // block).  The drafter catch-up runs the backlog's K/V and the last token's
-// q this way: one launch instead of two back to back.
+// q this way, and a drafter layer over up to 16 tokens the K/V and q of all
+// of them: one launch instead of two (three, with the q slices' reduction)
+// back to back.
 template <int DH, int NBT1, int MAXC1, int PPU1, int NBT2, int MAXC2>
 __global__ __launch_bounds__(256) void prefill_pair_bf16(PrefillParams a1, PrefillParams a2,
                                                          int units1, int ks1, int z1,
@@ -428,7 +432,7 @@ wf_status_t launch_prefill(wf_dtype_t dt, const void *x, const void *w_k,
                                    x_ls, w_ls, c_ls);
     PrefillParams a{x, w_k, w_v, k_cache, v_cache, n_tok, start_pos, cap, d_in,
                     n_kv_heads, {}, nullptr, 0, 1, x_ls, w_ls, c_ls, tiled ? 1 : 0, 2, 0,
-                    x_tiled ? 1 : 0};
+                    x_tiled ? 1 : 0, 0};
     for (int i = 0; i < head_dim / 2; ++i)
         a.theta[i] = std::pow(rope_base, -2.0 * (double)i / (double)head_dim);
     if (dt == WF_BF16) {
@@ -469,26 +473,30 @@ wf_status_t launch_prefill(wf_dtype_t dt, const void *x, const void *w_k,
     return WF_OK;
 }
 
-// The drafter catch-up's first two projections in one launch: the KV-only
-// prefill of the backlog's n_tok tiled rows (as launch_prefill with a tiled
-// x) and q = RoPE(W_q x_last) of the last token (as launch_q_rope), the
-// first set of exchange slots at the start of the zero block, the second at
-// its end.  WF_ERR_UNSUPPORTED when the two sets do not fit side by side (the
-// caller then launches the two one after the other).
-wf_status_t launch_prefill_and_q(bool tiled, const uint16_t *x_rows, const void *w_k,
-                                 const void *w_v, void *k_cache, void *v_cache, int n_tok,
-                                 int start_pos, int cap, int d_in, int n_kv_heads,
-                                 const uint16_t *x_last, const uint16_t *w_q, uint16_t *q,
+// A drafter layer's first projections in one launch: the KV-only prefill of
+// n_tok rows (as launch_prefill) and q = RoPE(W_q x) of n_q <= 16 rows at
+// positions q_pos, q_pos + 1, ... (as launch_q_rope for each), written to
+// q [n_q][n_q_heads][head_dim]; the first set of exchange slots at the start
+// of the zero block, the second at its end.  WF_ERR_UNSUPPORTED when the two
+// sets do not fit side by side (the caller then launches the two one after
+// the other).
+wf_status_t launch_prefill_and_q(bool tiled, const uint16_t *x_rows, bool x_tiled,
+                                 const void *w_k, const void *w_v, void *k_cache, void *v_cache,
+                                 int n_tok, int start_pos, int cap, int d_in, int n_kv_heads,
+                                 const uint16_t *x_q, int n_q, const uint16_t *w_q, uint16_t *q,
                                  int n_q_heads, int head_dim, int q_pos, double rope_base,
                                  void *workspace, hipStream_t stream) {
+    if (n_q < 1 || n_q > 16)
+        return WF_ERR_UNSUPPORTED;
     PrefillParams a1{x_rows, w_k, w_v, k_cache, v_cache, n_tok, start_pos, cap, d_in,
-                     n_kv_heads, {}, nullptr, 0, 1, 0, 0, 0, tiled ? 1 : 0, 2, 0, 1};
-    PrefillParams a2{x_last, w_q, w_q, q, q, 1, 0, 1, d_in, n_q_heads, {}, nullptr, 0, 1, 0, 0, 0,
-                     tiled ? 1 : 0, 1, q_pos, 0};
+                     n_kv_heads, {}, nullptr, 0, 1, 0, 0, 0, tiled ? 1 : 0, 2, 0,
+                     x_tiled ? 1 : 0, 0};
+    PrefillParams a2{x_q, w_q, w_q, q, q, n_q, 0, n_q, d_in, n_q_heads, {}, nullptr, 0, 1, 0, 0, 0,
+                     tiled ? 1 : 0, 1, q_pos, 0, n_q_heads};
     for (int i = 0; i < head_dim / 2; ++i)
         a1.theta[i] = a2.theta[i] = std::pow(rope_base, -2.0 * (double)i / (double)head_dim);
     const PrefillPlan p1 = plan_prefill(n_tok, d_in, n_kv_heads, head_dim, 1, 2, true);
-    const PrefillPlan p2 = plan_prefill(1, d_in, n_q_heads, head_dim, 1, 1);
+    const PrefillPlan p2 = plan_prefill(n_q, d_in, n_q_heads, head_dim, 1, 1);
     const size_t q_off = (kCounterBytes - prefill_slot_bytes(p2, 1)) / 256 * 256;
     if (prefill_slot_bytes(p2, 1) > kCounterBytes || prefill_slot_bytes(p1, 1) > q_off)
         return WF_ERR_UNSUPPORTED;
@@ -531,7 +539,7 @@ wf_status_t launch_q_rope(const uint16_t *x, const uint16_t *w_q, uint16_t *q, i
                           int n_heads, int head_dim, int pos, double rope_base,
                           void *workspace, hipStream_t stream, bool tiled) {
     PrefillParams a{x, w_q, w_q, q, q, 1, 0, 1, d_in, n_heads, {}, nullptr, 0, 1, 0, 0, 0,
-                    tiled ? 1 : 0, 1, pos, 0};
+                    tiled ? 1 : 0, 1, pos, 0, 0};
     for (int i = 0; i < head_dim / 2; ++i)
         a.theta[i] = std::pow(rope_base, -2.0 * (double)i / (double)head_dim);
     const PrefillPlan p = plan_prefill(1, d_in, n_heads, head_dim, 1, 1);

@@ -95,6 +95,11 @@ wf_status_t launch_linear_swiglu(const uint16_t *x, const uint16_t *w_gate,
 wf_status_t launch_linear_resid(const uint16_t *x, const uint16_t *w, const uint16_t *res,
                                 int k_in, int n_out, uint16_t *y, hipStream_t stream,
                                 bool tiled);
+// the same for up to 11 rows, y [rows][n_out]; WF_ERR_UNSUPPORTED for more
+// rows and for fewer features than fill the chip
+wf_status_t launch_linear_resid_rows(const uint16_t *x, const uint16_t *w, const uint16_t *res,
+                                     int rows, int k_in, int n_out, uint16_t *y,
+                                     hipStream_t stream, bool tiled);
 wf_status_t launch_linear_norm_swiglu(const uint16_t *x, const uint16_t *gain, float eps,
                                       const uint16_t *w_gate, const uint16_t *w_up, int k_in,
                                       int inter, uint16_t *act, hipStream_t stream,
@@ -186,10 +191,10 @@ wf_status_t launch_q_rope(const uint16_t *x, const uint16_t *w_q, uint16_t *q, i
 // The KV-only prefill of n_tok tiled rows and q = RoPE(W_q x_last) in one
 // launch (their exchange slots in the two halves of the zero block);
 // WF_ERR_UNSUPPORTED if they do not fit there.
-wf_status_t launch_prefill_and_q(bool tiled, const uint16_t *x_rows, const void *w_k,
-                                 const void *w_v, void *k_cache, void *v_cache, int n_tok,
-                                 int start_pos, int cap, int d_in, int n_kv_heads,
-                                 const uint16_t *x_last, const uint16_t *w_q, uint16_t *q,
+wf_status_t launch_prefill_and_q(bool tiled, const uint16_t *x_rows, bool x_tiled,
+                                 const void *w_k, const void *w_v, void *k_cache, void *v_cache,
+                                 int n_tok, int start_pos, int cap, int d_in, int n_kv_heads,
+                                 const uint16_t *x_q, int n_q, const uint16_t *w_q, uint16_t *q,
                                  int n_q_heads, int head_dim, int q_pos, double rope_base,
                                  void *workspace, hipStream_t stream);
 
