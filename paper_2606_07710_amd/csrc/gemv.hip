@@ -160,11 +160,11 @@ __global__ __launch_bounds__(kGemvWaves * kWave) void linear_partial_bf16(
 // the workgroup and no slices are stored and added by a second kernel.  Loads
 // and waves as in linear_partial_bf16; the row block's other MFMA columns come
 // for free.  What it saves is the store, the read and the launch of the slices
-// (drafter layer, d 4096, 8 rows: 103.5 -> 92.8 us with K, V and q in one
-// launch, some 7 us of it theirs; 2 rows: 96.2 -> 85.7).  The rule's two ends: from 12 rows on the
-// slices' workgroups read x once per 64 features, which this one reads once
-// per 16 (d 5120, 16 rows: 120.7 us with slices, 128.3 with this kernel), and fewer than
-// 256 blocks would leave CUs idle.
+// (drafter layer, d 4096, 8 rows: 103.5 -> 92.9 us with K, V and q in one
+// launch, some 7 us of it theirs; 2 rows: 96.2 -> 85.7).  The rule's two ends:
+// from 12 rows on the slices' workgroups read x once per 64 features, which
+// this one reads once per 16 (d 5120, 16 rows: 112.7 us with slices, 128.3
+// with this kernel), and fewer than 256 blocks would leave CUs idle.
 __global__ __launch_bounds__(kGemvWaves * kWave) void linear_resid_rows_bf16(
     const uint16_t *__restrict__ x, const uint16_t *__restrict__ w,
     const uint16_t *__restrict__ res, uint16_t *__restrict__ y, int rows, int k_in, int n_out,
