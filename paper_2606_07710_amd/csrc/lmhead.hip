@@ -550,7 +550,7 @@ template <int NB, int WF, int WK, int NBUF>
 __global__ __launch_bounds__(64 * WF * WK) void lm_gemm_bf16(const uint16_t *__restrict__ h,
                                                              const uint16_t *__restrict__ w,
                                                              LmFinish f, int d, int vocab) {
-    using G = TileGemm<2, NB, WF, 1, WK, NBUF, true>;
+    using G = TileGemm<2, NB, WF, 1, WK, NBUF, true, true>;
     __shared__ __attribute__((aligned(1024))) char ring[NBUF * G::STAGE];
     __shared__ RowState wst[WF][16 * NB];
     const int gamma = f.gamma;
@@ -656,27 +656,28 @@ __global__ __launch_bounds__(512) void lm_rows_bf16(const uint16_t *__restrict__
     const int r8 = 8 * hf + lane / 8;                  // row of the block
     const unsigned gran = ((lane & 7) ^ ((r8 >> 1) & 7)) * 16;
     const int xj = min(wave, XL - 1), xb = xj >> 1, xr8 = 8 * (xj & 1) + lane / 8;
-    const unsigned xoff = (unsigned)(min(16 * xb + xr8, gamma - 1) * ld) +
-                          ((lane & 7) ^ ((xr8 >> 1) & 7)) * 16;
+    // (64-bit addresses per lane: any hidden size)
+    const char *xsrc = reinterpret_cast<const char *>(h) + min(16 * xb + xr8, gamma - 1) * ld +
+                       ((lane & 7) ^ ((xr8 >> 1) & 7)) * 16;
     const char *wsrc[2];
-    unsigned woff[2];
     int is_sub = 0, is_st = 0, is_buf = 0;             // next stage to issue
     auto set_sub = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             // (a block past the run repeats its last one, which is in L2)
             const int blk = min(b0 + 8 * is_sub + bw + 4 * k, b1 - 1);
-            wsrc[k] = reinterpret_cast<const char *>(w) + blk * block_bytes + (TILED ? hf * 1024 : 0);
-            woff[k] = TILED ? lane * 16 : (unsigned)(min(r8, vocab - 1 - 16 * blk) * ld) + gran;
+            wsrc[k] = reinterpret_cast<const char *>(w) + blk * block_bytes +
+                      (TILED ? (size_t)(hf * 1024 + lane * 16)
+                             : min(r8, vocab - 1 - 16 * blk) * ld + gran);
         }
     };
     auto issue = [&]() __attribute__((always_inline)) {
         const unsigned slot = lds_addr(ring) + is_buf * STAGE;
         const size_t at = (size_t)is_st * (kGemmStep * 2);
         const size_t wat = TILED ? (size_t)is_st * 2048 : at;
-        lds_dma16_so<true>(wsrc[0] + wat, woff[0], slot + wave * 1024);
-        lds_dma16_so<true>(wsrc[1] + wat, woff[1], slot + (8 + wave) * 1024);
-        lds_dma16_so<false>(reinterpret_cast<const char *>(h) + at, xoff, slot + (16 + xj) * 1024);
+        lds_dma16<true>(wsrc[0] + wat, slot + wave * 1024);
+        lds_dma16<true>(wsrc[1] + wat, slot + (8 + wave) * 1024);
+        lds_dma16<false>(xsrc + at, slot + (16 + xj) * 1024);
         is_buf = is_buf + 1 == kRowsBuf ? 0 : is_buf + 1;
         if (++is_st == n_steps) {
             is_st = 0;
@@ -830,7 +831,7 @@ __global__ __launch_bounds__(kLmF32Waves * kWave) void lm_tiles_f32(
         // (VEC == 4 only where d % 4 == 0: a lane's four floats are all
         // inside the row or all outside)
 #pragma unroll 1
-        for (int c = lane * VEC; c < d; c += kWave * VEC) {
+        for (unsigned c = lane * VEC; c < (unsigned)d; c += kWave * VEC) {
             float wv[RV][VEC], hv[NR][VEC];
             auto load = [&](const float *p, float (&v)[VEC]) {
                 if constexpr (VEC == 4) {
@@ -909,8 +910,8 @@ __global__ __launch_bounds__(256) void lm_tiles_f32_many(const float *__restrict
 #pragma unroll
     for (int k = 0; k < kRowsPerThread; ++k)
         acc[k] = 0.f;
-    for (int c0 = 0; c0 < d; c0 += KC) {
-        const int kc = min(KC, d - c0);
+    for (unsigned c0 = 0; c0 < (unsigned)d; c0 += KC) {
+        const int kc = min((unsigned)KC, d - c0);
         float hv[NL], wv_[NL];
 #pragma unroll
         for (int u = 0; u < NL; ++u) {

@@ -36,8 +36,11 @@ struct GemmBlock {
 
 // NT: W with the non-temporal hint (each workgroup the only reader of its
 // W rows; the whole-line copies ask for each line once).
-template <int FB, int NB, int WF, int WT, int WK, int NBUF, bool NT>
+// FAR: any input dimension.  Else a block's offsets are 32-bit, for input
+// dimensions below 2^26.
+template <int FB, int NB, int WF, int WT, int WK, int NBUF, bool NT, bool FAR = false>
 struct TileGemm {
+    using Off = std::conditional_t<FAR, long long, int>;
     static constexpr int WAVES = WF * WT * WK;
     static constexpr int HPW = 2 / WK;                   // 32-dim halves per wave and step
     static constexpr int FBLK = FB * WF, TBLK = NB * WT; // 16-row blocks per workgroup
@@ -72,8 +75,8 @@ struct TileGemm {
         // stage; blocks [0, FBLK) are W, the rest x (the last waves may repeat
         // the last load, so that every wave counts the same number)
         const char *base[LPW];
-        unsigned voff[LPW];
-        int step_bytes[LPW], last_off[LPW];      // bytes per step, offset of the last step
+        std::conditional_t<FAR, size_t, unsigned> voff[LPW];
+        Off step_bytes[LPW], last_off[LPW];      // bytes per step, offset of the last step
         const size_t ld = (size_t)d_in * 2;
         // (an input dimension of 32 has no second half to read: it repeats the
         // first, and only the copy in the second half's place counts)
@@ -88,27 +91,33 @@ struct TileGemm {
                 base[i] = b.p + (one_half ? 0 : hf * 1024);
                 voff[i] = lane * 16;
                 step_bytes[i] = 2048;
-                last_off[i] = max(d_in / 32 - 2, 0) * 1024;
+                last_off[i] = (Off)max(d_in / 32 - 2, 0) * 1024;
             } else {
                 const int r = 8 * hf + lane / 8;             // row of the block
                 const int g = (lane & 7) ^ ((r >> 1) & 7);   // granule of the row's line
                 base[i] = b.p;
-                voff[i] = (unsigned)(min(r, b.rows - 1) * ld) + (one_half ? g & 3 : g) * 16;
+                voff[i] = min(r, b.rows - 1) * ld + (one_half ? g & 3 : g) * 16;
                 step_bytes[i] = kGemmStep * 2;
-                last_off[i] = max(d_in - kGemmStep, 0) * 2;
+                last_off[i] = (Off)max(d_in - kGemmStep, 0) * 2;
             }
         }
         // an input dimension of 64k + 32 ends with a step over its last 64 dims,
         // of which only the second half counts
-        const int n_steps = (d_in + kGemmStep - 1) / kGemmStep;
         const bool half_tail = d_in % kGemmStep != 0;
+        const int n_steps = d_in / kGemmStep + half_tail;
         auto issue = [&](int st, int buf) __attribute__((always_inline)) {
             const unsigned slot = lds_addr(ring) + buf * STAGE;
 #pragma unroll
             for (int i = 0; i < LPW; ++i) {
                 const int j = min(wave + WAVES * i, NLOAD - 1);
                 const char *src = base[i] + min(st * step_bytes[i], last_off[i]);
-                if (NT && j / 2 < FBLK)
+                const bool nt = NT && j / 2 < FBLK;
+                if constexpr (FAR) {
+                    if (nt)
+                        lds_dma16<true>(src + voff[i], slot + j * 1024);
+                    else
+                        lds_dma16<false>(src + voff[i], slot + j * 1024);
+                } else if (nt)
                     lds_dma16_so<true>(src, voff[i], slot + j * 1024);
                 else
                     lds_dma16_so<false>(src, voff[i], slot + j * 1024);

@@ -52,4 +52,24 @@ __device__ __forceinline__ void lds_dma16_so(const char *base, unsigned voff, un
                      : "memory", "m0");
 }
 
+// The same with a 64-bit address per lane, for sources whose rows can lie
+// 4 GB apart.
+template <bool NT = false>
+__device__ __forceinline__ void lds_dma16(const char *src, unsigned lds) {
+    if constexpr (NT)
+        asm volatile("s_mov_b32 m0, %1\n\t"
+                     "s_nop 0\n\t"
+                     "global_load_lds_dwordx4 %0, off nt"
+                     :
+                     : "v"(src), "s"(lds)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %1\n\t"
+                     "s_nop 0\n\t"
+                     "global_load_lds_dwordx4 %0, off"
+                     :
+                     : "v"(src), "s"(lds)
+                     : "memory", "m0");
+}
+
 }  // namespace wf

@@ -71,3 +71,28 @@ def test_masked_and_infinite_logits(gamma, d):
     got = np.array([keep.index(int(a)) for a in am.cpu()])
     check_argmax(got, am_ref, margin, z, "bf16")
     assert entropy_rel_err(ent.cpu().numpy(), ent_ref) <= 1e-5
+
+
+@pytest.mark.parametrize("gamma,d,vocab,tiled", [
+    (64, (1 << 25) + (1 << 22), 20, False),     # 64 rows of h span more than 4 GB
+    (64, (1 << 25) + (1 << 22), 20, True),
+    (2, 150000000, 16, False),                  # a 16-row block of W does
+])
+def test_rows_more_than_4gb_apart(gamma, d, vocab, tiled):
+    """Byte offsets past 32 bits, with inputs that are zero but for a few
+    whole numbers, so that every logit is exact in any order of sums."""
+    print(f"lmhead far rows gamma={gamma} d={d} vocab={vocab} tiled={tiled}", flush=True)
+    gen = torch.Generator().manual_seed(d)
+    cols = torch.tensor([0, 31, 515, d // 2 + 7, d - 33, d - 1])
+    hs = torch.randint(-3, 4, (gamma, len(cols)), generator=gen).double()
+    ws = torch.randint(-3, 4, (vocab, len(cols)), generator=gen).double()
+    h = torch.zeros(gamma, d, dtype=torch.bfloat16, device=DEV)
+    w = torch.zeros(vocab, d, dtype=torch.bfloat16, device=DEV)
+    h[:, cols.to(DEV)] = hs.to(DEV, torch.bfloat16)
+    w[:, cols.to(DEV)] = ws.to(DEV, torch.bfloat16)
+    am, ent, _ = _run(h, wf.tile_weights(w) if tiled else w)
+    z = hs @ ws.t()
+    # equal logits: the lowest index
+    assert torch.equal(am.cpu(), (z == z.amax(1, keepdim=True)).int().argmax(1).int())
+    lp = torch.log_softmax(z, 1)
+    assert entropy_rel_err(ent.cpu().numpy(), (-(lp.exp() * lp).sum(1)).numpy()) <= 1e-5
