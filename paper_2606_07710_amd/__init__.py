@@ -289,8 +289,8 @@ def wf_verify_attn(q, k_cache, v_cache, out, ctx_len, softmax_scale=None,
             code, gamma, ctx_len, hq, hkv, dh, num_splits), q.device)
     st = lib.wf_verify_attn(code, _dev(q, "q"), _dev(k_cache, "k_cache"),
                             _dev(v_cache, "v_cache"), _dev(out, "out"), gamma,
-                            int(ctx_len), cap, hq, hkv, dh,
-                            float(softmax_scale), int(num_splits),
+                            ctx_len, cap, hq, hkv, dh,
+                            float(softmax_scale), num_splits,
                             _dev(workspace, "workspace"), workspace.numel(),
                             _stream(stream))
     _check(st, "wf_verify_attn")
@@ -412,8 +412,8 @@ def wf_verify_attn_tree(q, k_cache, v_cache, out, ctx_len, tree_mask,
     st = lib.wf_verify_attn_tree(code, _dev(q, "q"), _dev(k_cache, "k_cache"),
                                  _dev(v_cache, "v_cache"), _dev(out, "out"),
                                  _dev(tree_mask, "tree_mask"), gamma,
-                                 int(ctx_len), cap, hq, hkv, dh,
-                                 float(softmax_scale), int(num_splits),
+                                 ctx_len, cap, hq, hkv, dh,
+                                 float(softmax_scale), num_splits,
                                  _dev(workspace, "workspace"),
                                  workspace.numel(), _stream(stream))
     _check(st, "wf_verify_attn_tree")
