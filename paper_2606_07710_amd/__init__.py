@@ -514,6 +514,9 @@ def decoder_layer(weights, n_q_heads, n_kv_heads, rms_eps, rope_base):
     head_dim = w_q.shape[0] // n_q_heads
     if w_k.shape[0] != n_kv_heads * head_dim:
         raise ValueError("w_k rows must be n_kv_heads * head_dim")
+    for n in DECODER_WEIGHTS:
+        if weights[n] is None:
+            raise ValueError(f"{n} is missing")
     layer = DecoderLayer(*[_dev(weights[n], n) for n in DECODER_WEIGHTS],
                          w_q.shape[1], n_q_heads, n_kv_heads, head_dim,
                          w_gate.shape[0], float(rms_eps), float(rope_base))

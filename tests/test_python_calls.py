@@ -56,3 +56,13 @@ def test_attention_reaches_the_library(tree):
     with pytest.raises(wf.WfError) as e:
         _attend(tree, 5)
     assert e.value.status == wf.WF_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("missing", ["attn_norm", "w_v", "w_down"])
+def test_a_decoder_layer_needs_every_weight(missing):
+    w = {n: FakeTensor(*((256,) if n.endswith("norm") else (256, 256)))
+         for n in wf.DECODER_WEIGHTS}
+    assert wf.decoder_layer(w, 2, 2, 1e-6, 1e4).hidden == 256
+    w[missing] = None
+    with pytest.raises((ValueError, AttributeError)):
+        wf.decoder_layer(w, 2, 2, 1e-6, 1e4)
