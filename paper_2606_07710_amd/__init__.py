@@ -230,9 +230,16 @@ def _dev(t, name):
 
 # The current device's current stream as a raw handle: torch.cuda's own
 # current_stream() builds a Stream object around it, 2.7 us of a call that
-# takes about 3 on the host besides its kernel launches.
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_device = torch._C._cuda_getDevice
+# takes about 3 on the host besides its kernel launches.  The getters are
+# private to torch: a torch without them takes the public way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+if _raw_stream is None or _device is None:
+    def _raw_stream(_):
+        return torch.cuda.current_stream().cuda_stream
+
+    def _device():
+        return None
 
 
 def _stream(stream):

@@ -2,11 +2,16 @@
 tensors whose pointers the C side refuses (not 16-byte aligned), so no call
 ever reaches the GPU."""
 import ctypes
+import os
+import subprocess
+import sys
 
 import pytest
 import torch
 
 wf = pytest.importorskip("paper_2606_07710_amd")
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 class FakeTensor:
@@ -66,3 +71,19 @@ def test_a_decoder_layer_needs_every_weight(missing):
     w[missing] = None
     with pytest.raises((ValueError, AttributeError)):
         wf.decoder_layer(w, 2, 2, 1e-6, 1e4)
+
+
+def test_import_without_torch_private_functions():
+    """A torch without the two private stream getters: the package imports and
+    takes the stream from torch.cuda.current_stream()."""
+    code = """
+import torch
+for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+    if hasattr(torch._C, n):
+        delattr(torch._C, n)
+import paper_2606_07710_amd as wf
+class S: cuda_stream = 77
+torch.cuda.current_stream = lambda: S
+assert wf._stream(None) == 77
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=300)
