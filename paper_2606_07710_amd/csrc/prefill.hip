@@ -426,7 +426,7 @@ wf_status_t launch_prefill(wf_dtype_t dt, const void *x, const void *w_k,
         dt = WF_BF16;
     if (x_tiled && dt != WF_BF16)
         return WF_ERR_UNSUPPORTED;
-    if (dt == WF_BF16 && prefill_gemm_takes(n_tok, d_in, n_kv_heads, head_dim, n_layers))
+    if (dt == WF_BF16 && prefill_gemm_takes(n_tok, d_in, n_kv_heads, head_dim, n_layers, tiled))
         return launch_prefill_gemm(tiled, x_tiled, x, w_k, w_v, k_cache, v_cache, n_tok, start_pos,
                                    cap, d_in, n_kv_heads, head_dim, rope_base, stream, n_layers,
                                    x_ls, w_ls, c_ls);

@@ -155,10 +155,40 @@ struct GemmTile {
 
 constexpr int kComputeUnits = 256;
 
+// Whether prefill.hip's kernel, which splits the input dimension over
+// workgroups, is faster than one workgroup walking all of it.  That walk is a
+// serial chain: about 3.6 us and 3.0 (tiled W) or 2.8 us per 1024 dims as long
+// as the tiles fit the chip in one round.  The split kernel's chain is ks times
+// shorter, but costs an exchange per halving and more per dim; both lines, per
+// plan, are fits to calls of 65 to 320 tokens over 1024 to 8192 dims and 1 to
+// 16 KV heads.  Split -> whole, us, tiled W unless stated: 8 heads of 128, 81
+// tokens, 4096 dims 13.7 -> 15.6, 5120: 15.4 -> 19.9, 2560: 11.9 -> 10.8; 128
+// tokens, 4096: 16.0 -> 15.9, row-major 20.4 -> 15.0; 2 heads, 4096 dims, 128
+// tokens 11.8 -> 15.9, 256: 15.7 -> 14.9; 2 layers of 1 head, 80 tokens 8.7 ->
+// 15.9.  Without a split the whole walk is always the faster.
+bool split_is_faster(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers,
+                     bool w_tiled) {
+    const PrefillPlan p = plan_prefill(n_tok, d_in, n_kv_heads, head_dim, n_layers);
+    if (p.ksplit == 1)
+        return false;
+    // us: constant, per halving, per 1024 dims of a slice (tiled, row-major W)
+    struct Line {
+        double base, level, tiled, row_major;
+    };
+    const Line l = p.ppu == 2 ? (p.nbt <= 3 ? Line{5.8, 1.4, 4.5, 6.3} : Line{8.7, 1.3, 5.0, 7.2})
+                              : (p.nbt <= 3 ? Line{5.0, 0.6, 3.5, 4.6} : Line{6.0, 0.5, 4.8, 5.9});
+    const double kdims = d_in / 1024.0;
+    const double split = l.base + l.level * std::log2(p.ksplit) +
+                         (w_tiled ? l.tiled : l.row_major) * kdims / p.ksplit;
+    return split < 3.6 + (w_tiled ? 3.0 : 2.8) * kdims;
+}
+
 // The tile for a call, or false where the split-K kernel of prefill.hip is
 // the better one (us per call, head_dim 128, 8 KV heads, 4096 dims unless
 // stated; that kernel's time -> this one's).
-bool pick_tile(int n_tok, int feats, int n_layers, GemmTile &t) {
+bool pick_tile(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers, bool w_tiled,
+               GemmTile &t) {
+    const int feats = 2 * n_kv_heads * head_dim;
     const int blocks16 = cdiv(n_tok, 16);
     const long long units = (long long)n_layers * cdiv(feats, 32);
     // All tokens in one block, many layers: the call streams W once, with
@@ -167,14 +197,22 @@ bool pick_tile(int n_tok, int feats, int n_layers, GemmTile &t) {
     // block), as long as a few workgroups per CU remain; fewer stages where
     // many workgroups share a CU.  36 layers: 16 tokens 124 -> 92 (64
     // features 98, 128: 103), 32: 150 -> 100 (32: 110, 128: 106), 48: 177 ->
-    // 113, 80: 258 -> 125, 128: 355 -> 155; 12 layers: 10 tokens 40 -> 34,
-    // 32: 54 -> 41; 8 layers: 16 tokens 30 -> 24, 80: 61 -> 31.  Fewer
-    // layers leave it latency-bound (4 layers: 16 tokens 17 -> 20, 32: 16 ->
-    // 21): there the input dimension has to be split over workgroups.
+    // 113, 80: 258 -> 125, 128: 355 -> 155; 12 layers: 10 tokens 40 -> 34, 32:
+    // 54 -> 41; 8 layers: 16 tokens 30 -> 24,
+    // 80: 61 -> 31.  Fewer layers leave it latency-bound (4 layers: 16 tokens
+    // 17 -> 20, 32: 16 -> 21): there the input dimension has to be split over
+    // workgroups.
     if (blocks16 <= 8) {
         const int nb = blocks16 == 7 ? 8 : blocks16;
-        if (blocks16 == 1 && units >= 512) {
-            t = {2, 1, 1, 1, 2, units >= 4 * kComputeUnits ? 2 : 4};
+        // one token block over a short tiled W: the split kernel has all of a
+        // wave's loads in flight in one or two round trips (8 tokens, 64
+        // layers of 512 features: 1024 dims 14.5 -> 17.0; 512 units of 2048
+        // dims 14.2 -> 15.5, 640: 18.6 -> 17.6)
+        const int min1 = !w_tiled || d_in > 2048 ? 512 : d_in > 1024 ? 640 : INT32_MAX;
+        if (blocks16 == 1 && units >= min1) {
+            // (a CU's LDS holds six workgroups of four stages; 1024 units, 1
+            // token: two stages 54.7 us, four 45; 2048: 87 and 91)
+            t = {2, 1, 1, 1, 2, units > 6 * kComputeUnits ? 2 : 4};
             return true;
         }
         if (blocks16 >= 4 && units >= 8 * kComputeUnits) {
@@ -193,11 +231,10 @@ bool pick_tile(int n_tok, int feats, int n_layers, GemmTile &t) {
     // 1013: 43.8 -> 25.1 (row-major W 62 -> 26), 2048: 78.7 -> 40.2, 4096:
     // 154 -> 69.7, where the matrix cores run at 990 TFLOP/s; the next
     // smaller tile 20.6, 30.6, 47.8 and 86.2 from 512 tokens on).  Up to 80
-    // tokens the split over the input dimension is as fast or faster (13.3
-    // against 13.3 at 80, 6.5 at 16).
-    if (n_tok <= 80 && n_layers == 1)
-        return false;
-    if (n_tok <= 64)
+    // tokens of one layer the split over the input dimension is as fast or
+    // faster (13.3 against 13.3 at 80, 6.5 at 16).
+    if (n_tok <= (n_layers == 1 ? 80 : 64) ||
+        split_is_faster(n_tok, d_in, n_kv_heads, head_dim, n_layers, w_tiled))
         return false;
     for (const GemmTile c : {GemmTile{2, 1, 2, 2, 1, 4}, GemmTile{2, 2, 2, 2, 2, 4},
                              GemmTile{4, 2, 2, 2, 2, 3}, GemmTile{2, 4, 4, 2, 1, 3},
@@ -212,11 +249,12 @@ bool pick_tile(int n_tok, int feats, int n_layers, GemmTile &t) {
 
 }  // namespace
 
-bool prefill_gemm_takes(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers) {
+bool prefill_gemm_takes(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers,
+                        bool w_tiled) {
     GemmTile t;
     // (offsets within a 16-row block are 32-bit)
     return 32LL * d_in < (1LL << 31) &&
-           pick_tile(n_tok, 2 * n_kv_heads * head_dim, n_layers, t);
+           pick_tile(n_tok, d_in, n_kv_heads, head_dim, n_layers, w_tiled, t);
 }
 
 wf_status_t launch_prefill_gemm(bool w_tiled, bool x_tiled, const void *x, const void *w_k,
@@ -225,7 +263,7 @@ wf_status_t launch_prefill_gemm(bool w_tiled, bool x_tiled, const void *x, const
                                 double rope_base, hipStream_t stream, int n_layers,
                                 long long x_ls, long long w_ls, long long c_ls) {
     GemmTile t;
-    if (!pick_tile(n_tok, 2 * n_kv_heads * head_dim, n_layers, t))
+    if (!pick_tile(n_tok, d_in, n_kv_heads, head_dim, n_layers, w_tiled, t))
         return WF_ERR_UNSUPPORTED;
     GemmParams a{};
     a.x = static_cast<const char *>(x);

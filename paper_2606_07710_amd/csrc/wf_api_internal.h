@@ -166,7 +166,8 @@ wf_status_t launch_prefill(wf_dtype_t dt, const void *x, const void *w_k,
 
 // The same product as an LDS-tiled kernel for many tokens or many layers
 // (prefill_gemm.hip); needs no workspace.
-bool prefill_gemm_takes(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers);
+bool prefill_gemm_takes(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers,
+                        bool w_tiled);
 wf_status_t launch_prefill_gemm(bool w_tiled, bool x_tiled, const void *x, const void *w_k,
                                 const void *w_v, void *k_cache, void *v_cache, int n_tok,
                                 int start_pos, int cap, int d_in, int n_kv_heads, int head_dim,

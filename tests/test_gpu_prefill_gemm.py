@@ -58,6 +58,26 @@ def test_one_layer(n, d, hkv, dh, tiled):
     _check(1, n, d, hkv, dh, 70001, tiled, (0,))
 
 
+# more tokens, but few heads and long inputs: the kernel that splits the input
+# dimension takes them back.  Both sides of that line, for one layer (units of
+# two pairs, three and four token blocks) and for two to four
+FEW_HEADS = [
+    # layers, n, d, hkv, dh, tiled, layers checked
+    (1, 81, 4096, 2, 128, True, (0,)), (1, 97, 4096, 2, 128, False, (0,)),
+    (1, 160, 4096, 1, 128, True, (0,)), (1, 161, 4096, 1, 128, True, (0,)),
+    (1, 301, 4096, 1, 128, True, (0,)), (1, 200, 8192, 2, 64, True, (0,)),
+    (1, 175, 8192, 2, 64, False, (0,)), (1, 640, 4096, 1, 128, True, (0,)),
+    (2, 65, 4096, 1, 128, False, (1,)), (3, 80, 4096, 1, 64, True, (0, 2)),
+    (4, 129, 4096, 1, 64, True, (3,)), (2, 250, 4096, 1, 128, True, (1,)),
+    (2, 65, 512, 1, 128, True, (1,)),
+]
+
+
+@pytest.mark.parametrize("L,n,d,hkv,dh,tiled,check", FEW_HEADS)
+def test_few_heads(L, n, d, hkv, dh, tiled, check):
+    _check(L, n, d, hkv, dh, 500, tiled, check)
+
+
 # many layers: every token-block count of the streaming tiles, the lines at
 # 384, 512, 1024 and 2048 units of 32 features, and two token blocks
 MANY = [
@@ -71,6 +91,10 @@ MANY = [
     (40, 128, 64, 8, 128, True, (39,)), (37, 33, 96, 5, 64, False, (36,)),
     (75, 120, 96, 3, 64, True, (74,)), (36, 129, 96, 8, 128, False, (35,)),
     (3, 200, 96, 8, 128, True, (2,)),
+    # one token block around the unit counts of short tiled inputs and of four stages
+    (16, 16, 1056, 8, 64, True, (15,)), (20, 16, 1056, 8, 64, True, (0, 19)),
+    (24, 9, 96, 8, 128, False, (23,)), (25, 9, 96, 8, 128, False, (24,)),
+    (24, 16, 2080, 8, 128, True, (23,)), (25, 3, 2080, 8, 128, True, (24,)),
 ]
 
 
