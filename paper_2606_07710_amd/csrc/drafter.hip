@@ -38,7 +38,6 @@ namespace {
 
 constexpr int kNormThreads = 256;
 constexpr int kMaxHalfDim = 64;
-constexpr int kPairMaxTokens = 768;
 
 struct RopeParams {
     double theta[kMaxHalfDim];   // base^(-2i/D), i < D/2, formed on the host in fp64
@@ -400,13 +399,17 @@ wf_status_t launch_drafter_catchup(const wf_decoder_layer_t &L, const void *r, i
     rmsnorm_bf16<<<(n + 15) / 16 * 16, kNormThreads, 0, stream>>>(
         rb, static_cast<const uint16_t *>(L.attn_norm), L.rms_eps, xnb, d, n, xnt);
     // A short backlog: its K/V and the last token's q in one launch (they
-    // only share the normalised rows).  Beyond kPairMaxTokens the K/V take
-    // the LDS-tiled kernel and q a launch of its own (whole catch-up, 4096
-    // cached rows: 256 tokens 93.5 us in one launch against 98.7, 700: 108.3
-    // against 109.2, 1024: 111.8 against 112.1 tiled and 151.5 against 135.9
-    // row-major, 2048: 147.7 against 141.2).
+    // only share the normalised rows); beyond it the K/V take the LDS-tiled
+    // kernel and q a launch of its own.  Row-major W, which that kernel reads
+    // in whole lines, changes over first.  Whole catch-up, us, one launch ->
+    // two, 1000 cached rows; tiled: d 4096, 768 tokens 107.0 -> 107.9, 1024:
+    // 110.6 -> 112.8, 1300: 125.1 -> 123.6; d 5120, 769: 127.0 -> 139.2, 1300:
+    // 155.1 -> 151.3; d 1024, 700: 38.9 -> 37.7, 1024: 40.9 -> 38.3; row-major:
+    // d 4096, 256: 115.9 -> 119.0, 512: 126.8 -> 122.0, 700: 141.5 -> 129.8;
+    // with 2 KV heads 512: 116.2 -> 120.6, 700: 121.0 -> 121.2.
+    const int pair_max = !tiled ? 512 : d < 2048 ? 768 : 1024;
     bool q_ready = false;
-    if (n <= kPairMaxTokens) {
+    if (n <= pair_max) {
         const wf_status_t st = launch_prefill_and_q(
             tiled, xnt, true, L.w_k, L.w_v, k_cache, v_cache, n, pos, cap, d, L.n_kv_heads, x_last,
             1, static_cast<const uint16_t *>(L.w_q),

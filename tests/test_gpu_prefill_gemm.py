@@ -107,7 +107,20 @@ def test_many_layers(L, n, d, hkv, dh, tiled, check):
 def test_catchup_hands_over_tiled_rows(n):
     """A drafter catch-up around the backlog from which its K/V run in the
     LDS-tiled kernel, reading the RMSNorm launch's tiled rows."""
-    hid, hq, hkv, dh, inter, pos = 288, 4, 2, 64, 320, 9
+    _check_catchup(n, 288, False)
+
+
+@pytest.mark.parametrize("n,hid,tiled", [(512, 288, False), (513, 288, False), (768, 288, True),
+                                         (769, 288, True), (1024, 2048, True),
+                                         (1025, 2048, True)])
+def test_catchup_changes_over(n, hid, tiled):
+    """The backlogs at which the launches change, per weight layout and width."""
+    _check_catchup(n, hid, tiled)
+
+
+def _check_catchup(n, hid, tiled):
+    print(f"catch-up n={n} hidden={hid} tiled={tiled}", flush=True)
+    hq, hkv, dh, inter, pos = 4, 2, 64, 320, 9
     shapes = {"attn_norm": (hid,), "w_q": (hq * dh, hid), "w_k": (hkv * dh, hid),
               "w_v": (hkv * dh, hid), "w_o": (hid, hq * dh), "mlp_norm": (hid,),
               "w_gate": (inter, hid), "w_up": (inter, hid), "w_down": (hid, inter)}
@@ -118,7 +131,8 @@ def test_catchup_hands_over_tiled_rows(n):
     vc = W.normal((hkv, pos + n + 1, dh), 1.0, 52, BF, DEV)
     kh, vh = W.to_oracle(kc), W.to_oracle(vc)
     out = torch.empty(hid, dtype=BF, device=DEV)
-    wf.wf_drafter_catchup(wf.decoder_layer(w, hq, hkv, 1e-6, 1e6), r, pos, kc, vc, out)
+    given = {k: v if k.endswith("norm") or not tiled else wf.tile_weights(v) for k, v in w.items()}
+    wf.wf_drafter_catchup(wf.decoder_layer(given, hq, hkv, 1e-6, 1e6), r, pos, kc, vc, out)
     torch.cuda.synchronize()
     ref, kref, vref = oracle.catchup(W.to_oracle(r), pos, {k: W.to_oracle(v) for k, v in w.items()},
                                      kh, vh, hq, hkv, 1e-6, 1e6)
