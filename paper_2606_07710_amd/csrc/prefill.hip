@@ -524,8 +524,8 @@ wf_status_t launch_prefill_and_q(bool tiled, const uint16_t *x_rows, bool x_tile
     WF_PAIR_CASE(128, 1, M8, 1) WF_PAIR_CASE(128, 2, M8, 1) WF_PAIR_CASE(128, 3, M8, 1)
     WF_PAIR_CASE(128, 4, M8, 1) WF_PAIR_CASE(64, 1, M8, 1) WF_PAIR_CASE(64, 2, M8, 1)
     WF_PAIR_CASE(64, 3, M8, 1) WF_PAIR_CASE(64, 4, M8, 1)
-    WF_PAIR_CASE(128, 3, MW, 2) WF_PAIR_CASE(128, 4, MW, 2)
-    WF_PAIR_CASE(64, 3, MW, 2) WF_PAIR_CASE(64, 4, MW, 2)
+    // (beside q, two-pair units start at 384 tokens, so with four token blocks)
+    WF_PAIR_CASE(128, 4, MW, 2) WF_PAIR_CASE(64, 4, MW, 2)
     { return WF_ERR_UNSUPPORTED; }
 #undef WF_PAIR_CASE
     return hipGetLastError() == hipSuccess ? WF_OK : WF_ERR_HIP;

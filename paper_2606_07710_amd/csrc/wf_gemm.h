@@ -162,9 +162,8 @@ struct TileGemm {
                     acc[fb][nb] = mfma16x16x32(wr[P][fb], xr[P][nb], acc[fb][nb]);
         };
         auto wait_later = [&](int later) __attribute__((always_inline)) {
-            if (NBUF > 4 && later >= 4)
-                wait_vmcnt<(NBUF > 4 ? 4 : 0) * LPW>();
-            else if (NBUF > 3 && later >= 3)
+            static_assert(NBUF <= 4, "wait counts");
+            if (NBUF > 3 && later >= 3)
                 wait_vmcnt<(NBUF > 3 ? 3 : 0) * LPW>();
             else if (NBUF > 2 && later >= 2)
                 wait_vmcnt<(NBUF > 2 ? 2 : 0) * LPW>();
