@@ -12,7 +12,8 @@
 //                                              + reduce_rope_bf16
 //   a   = causal GQA attention over the cache  the verify-attention kernels
 //   h1  = r + Wo a                             skinny linear + reduce_store_bf16 (up to
-//                                              11 tokens: linear_resid_rows_bf16)
+//                                              11 tokens of a layer of 4096 or
+//                                              more: linear_resid_rows_bf16)
 //   xn2 = RMSNorm(h1) * g2                     rmsnorm_bf16
 //   act = SiLU(Wg xn2) * (Wu xn2)              one skinny linear over [Wg; Wu]
 //                                              + reduce_swiglu_bf16
@@ -25,8 +26,8 @@
 // epilogue instead: q = RoPE(Wq xn) on the KV-only prefill kernel (its
 // split-K exchange tree spreads the 32 MB over the chip), h1 = r + Wo a and
 // out = h1 + Wd act in one kernel each, and [Wg; Wu] with the MLP's RMSNorm
-// folded into its loads and SwiGLU into its epilogue -- 8 launches per
-// catch-up instead of 13.
+// folded into its loads and SwiGLU into its epilogue -- with the backlog's
+// K/V in q's launch, 7 launches per catch-up instead of 13.
 #include <cmath>
 
 #include "wf_api_internal.h"

@@ -40,9 +40,12 @@ struct GemmParams {
     double turns[kMaxHalfDim];           // RoPE frequencies in turns per position
 };
 
-// cos and sin of 2*pi*t.  The turn is reduced in fp64 (exact), then to the
-// nearest quarter in fp32 (exact), and the rest, at most pi/4 in size, goes
-// through the Taylor series (truncation below 3e-9).
+// cos and sin of 2*pi*t.  The turn is reduced in fp64 (exact) and rounded to
+// fp32, then reduced to the nearest quarter (exact), and the rest, at most pi/4
+// in size, goes through the Taylor series (truncation below 3e-9).  Against 64
+// bits over 2 million positions up to 70000: error at most 1.5e-7, 4.4e-8 in
+// the mean square; sincosf of the reduced angle, as the small-batch kernel
+// has it, 1.6e-7 and 4.7e-8.
 __device__ __forceinline__ void sincos_turns(double t, float &s, float &c) {
     const float f = (float)(t - rint(t));
     const float q = rintf(4.f * f);

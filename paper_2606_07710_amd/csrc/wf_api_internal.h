@@ -189,9 +189,10 @@ wf_status_t launch_q_rope(const uint16_t *x, const uint16_t *w_q, uint16_t *q, i
                           int n_heads, int head_dim, int pos, double rope_base,
                           void *workspace, hipStream_t stream, bool tiled);
 
-// The KV-only prefill of n_tok tiled rows and q = RoPE(W_q x_last) in one
-// launch (their exchange slots in the two halves of the zero block);
-// WF_ERR_UNSUPPORTED if they do not fit there.
+// The KV-only prefill of n_tok rows (x_tiled: in 16 x 32 tiles) and q =
+// RoPE(W_q x) of n_q <= 16 rows at positions q_pos on in one launch (their
+// exchange slots at the two ends of the zero block); WF_ERR_UNSUPPORTED if
+// they do not fit there.
 wf_status_t launch_prefill_and_q(bool tiled, const uint16_t *x_rows, bool x_tiled,
                                  const void *w_k, const void *w_v, void *k_cache, void *v_cache,
                                  int n_tok, int start_pos, int cap, int d_in, int n_kv_heads,
