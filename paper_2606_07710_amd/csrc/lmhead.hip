@@ -879,7 +879,7 @@ __global__ __launch_bounds__(kLmF32Waves * kWave) void lm_tiles_f32(
     tile_states(zs, f.states, blockIdx.x, f.n_tiles, v0, gamma, vocab, wave, kLmF32Waves, lane);
 }
 
-// fp32 LM head for more than 16 verify rows, or more than 8 over short rows.
+// fp32 LM head for more than 16 verify rows.
 // NR = verify rows per thread (rows rq, rq + 4, ...: ceil(gamma / 4) rounded
 // up to a power of two), a template parameter so the inner loop carries no
 // per-row branches.
@@ -1106,16 +1106,12 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
         const float *wf32 = static_cast<const float *>(w_lm);
         // up to two passes over a tile; with more rows W would come from L2
         // and beyond once per 8 rows (61 rows, d 4096, vocabulary 60000: 1276
-        // us staged in LDS, 1459 in passes; 16 rows: 588 and 383)
-        // (two passes also lose where a hidden size of one 128-dim stage meets a
-        // vocabulary of at most one tile per CU: 9 rows, d 100, vocabulary 500:
-        // 14.0 us staged, 15.6 in passes, d 32: 12.8 and 16.4; d 192: 17.3 and
-        // 15.5; d 100, vocabulary 32000: 23.2 and 20.6)
+        // us staged in LDS, 1459 in passes; 16 rows: 588 and 383).  (9 to 16
+        // rows of hidden sizes up to 128 lose by it, 9 rows, d 100: 15.6 us
+        // against 14.0, but its short sums are the more exact: entropy error
+        // 3.9e-7 against 1.2e-6 staged)
         const dim3 grid(f.n_tiles);
-        const bool staged = gamma > 8 && d <= 128 && f.n_tiles <= 256;
-        if (gamma <= 16 && staged)
-            lm_tiles_f32_many<4><<<grid, 256, 0, stream>>>(hf, wf32, f, d, vocab);
-        else if (gamma <= 16 && d % 4 == 0)
+        if (gamma <= 16 && d % 4 == 0)
             lm_tiles_f32<4><<<grid, kLmF32Waves * kWave, 0, stream>>>(hf, wf32, f, d, vocab);
         else if (gamma <= 16)
             lm_tiles_f32<1><<<grid, kLmF32Waves * kWave, 0, stream>>>(hf, wf32, f, d, vocab);

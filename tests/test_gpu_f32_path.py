@@ -34,14 +34,6 @@ def test_lmhead_f32(gamma, d, vocab):
     assert err <= 1e-4, float(err)
 
 
-@pytest.mark.parametrize("gamma", [8, 9, 12, 16, 17])
-@pytest.mark.parametrize("d,vocab", [(128, 16384), (128, 16385), (129, 500), (31, 65)])
-def test_lmhead_f32_short_rows(gamma, d, vocab):
-    """Where 9 to 16 verify rows are staged in LDS: rows of at most 128 floats
-    and at most 256 tiles of 64 vocabulary rows."""
-    test_lmhead_f32(gamma, d, vocab)
-
-
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("gamma,ctx,splits", [(1, 0, 0), (1, 63, 0), (1, 64, 1), (8, 55, 0),
                                               (8, 56, 0), (8, 57, 1), (5, 250, 2), (16, 1000, 3),
