@@ -547,11 +547,11 @@ __global__ __launch_bounds__(512) void lm_wide_bf16(const uint16_t *__restrict__
 // 2880, vocabulary 151936: 245 -> 140 us per call, 6.2 TB/s; 61 rows: 413 ->
 // 162).  For hidden sizes without a tiled-weights kernel: the sums and
 // states of the others are those of that kernel.
-template <int NB, int WF, int WK, int NBUF>
+template <int NB, int WF, int WK, int NBUF, bool FAR>
 __global__ __launch_bounds__(64 * WF * WK) void lm_gemm_bf16(const uint16_t *__restrict__ h,
                                                              const uint16_t *__restrict__ w,
                                                              LmFinish f, int d, int vocab) {
-    using G = TileGemm<2, NB, WF, 1, WK, NBUF, true, true>;
+    using G = TileGemm<2, NB, WF, 1, WK, NBUF, true, FAR>;
     __shared__ __attribute__((aligned(1024))) char ring[NBUF * G::STAGE];
     __shared__ RowState wst[WF][16 * NB];
     const int gamma = f.gamma;
@@ -625,9 +625,13 @@ __global__ __launch_bounds__(64 * WF * WK) void lm_gemm_bf16(const uint16_t *__r
 // 8 KB apart, so from few channels at a time; walking the dimensions from
 // another step in each workgroup took 215, but is another order of sums
 // than the tiled form's.)
+// FAR: a lane's offset within eight rows takes 64 bits (d >= kFarRows);
+// shorter rows keep it to 32 beside a wave-uniform base (61 rows, d 2560:
+// 150.3 us per call, with 64 bits 151.0 to 151.7).
 constexpr int kRowsBuf = 6;
+constexpr int kFarRows = 1 << 28;
 
-template <int NB, bool TILED>
+template <int NB, bool TILED, bool FAR>
 __global__ __launch_bounds__(512) void lm_rows_bf16(const uint16_t *__restrict__ h,
                                                     const uint16_t *__restrict__ w,
                                                     LmFinish f, int d, int vocab) {
@@ -657,28 +661,38 @@ __global__ __launch_bounds__(512) void lm_rows_bf16(const uint16_t *__restrict__
     const int r8 = 8 * hf + lane / 8;                  // row of the block
     const unsigned gran = ((lane & 7) ^ ((r8 >> 1) & 7)) * 16;
     const int xj = min(wave, XL - 1), xb = xj >> 1, xr8 = 8 * (xj & 1) + lane / 8;
-    // (64-bit addresses per lane: any hidden size)
-    const char *xsrc = reinterpret_cast<const char *>(h) + min(16 * xb + xr8, gamma - 1) * ld +
-                       ((lane & 7) ^ ((xr8 >> 1) & 7)) * 16;
+    using Off = std::conditional_t<FAR, size_t, unsigned>;
+    const int xr0 = min(16 * xb + 8 * (xj & 1), gamma - 1);
+    const char *xsrc = reinterpret_cast<const char *>(h) + xr0 * ld;
+    const Off xoff = (min(16 * xb + xr8, gamma - 1) - xr0) * ld +
+                     ((lane & 7) ^ ((xr8 >> 1) & 7)) * 16;
     const char *wsrc[2];
+    Off woff[2];
     int is_sub = 0, is_st = 0, is_buf = 0;             // next stage to issue
     auto set_sub = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
             // (a block past the run repeats its last one, which is in L2)
             const int blk = min(b0 + 8 * is_sub + bw + 4 * k, b1 - 1);
+            const int last = TILED ? 15 : vocab - 1 - 16 * blk, r0 = min(8 * hf, last);
             wsrc[k] = reinterpret_cast<const char *>(w) + blk * block_bytes +
-                      (TILED ? (size_t)(hf * 1024 + lane * 16)
-                             : min(r8, vocab - 1 - 16 * blk) * ld + gran);
+                      (TILED ? (size_t)hf * 1024 : r0 * ld);
+            woff[k] = TILED ? lane * 16 : (min(r8, last) - r0) * ld + gran;
         }
+    };
+    auto copy = [](auto nt, const char *base, Off off, unsigned lds) __attribute__((always_inline)) {
+        if constexpr (FAR)
+            lds_dma16<decltype(nt)::value>(base + off, lds);
+        else
+            lds_dma16_so<decltype(nt)::value>(base, off, lds);
     };
     auto issue = [&]() __attribute__((always_inline)) {
         const unsigned slot = lds_addr(ring) + is_buf * STAGE;
         const size_t at = (size_t)is_st * (kGemmStep * 2);
         const size_t wat = TILED ? (size_t)is_st * 2048 : at;
-        lds_dma16<true>(wsrc[0] + wat, slot + wave * 1024);
-        lds_dma16<true>(wsrc[1] + wat, slot + (8 + wave) * 1024);
-        lds_dma16<false>(xsrc + at, slot + (16 + xj) * 1024);
+        copy(std::true_type{}, wsrc[0] + wat, woff[0], slot + wave * 1024);
+        copy(std::true_type{}, wsrc[1] + wat, woff[1], slot + (8 + wave) * 1024);
+        copy(std::false_type{}, xsrc + at, xoff, slot + (16 + xj) * 1024);
         is_buf = is_buf + 1 == kRowsBuf ? 0 : is_buf + 1;
         if (++is_st == n_steps) {
             is_st = 0;
@@ -1054,12 +1068,15 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
         const uint16_t *hb = static_cast<const uint16_t *>(h);
         const uint16_t *wb = static_cast<const uint16_t *>(w_lm);
         const int nbl = cdiv(gamma, 16);
-#define WF_ROWS(NBLV)                                                                        \
-    if (nbl == NBLV && tiled) {                                                              \
-        lm_rows_bf16<NBLV, true><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab);        \
-    } else if (nbl == NBLV) {                                                                \
-        lm_rows_bf16<NBLV, false><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab);       \
+        const bool far = d >= kFarRows;
+#define WF_ROWS_AS(NBLV, TILEDV, FARV)                                                       \
+    if (nbl == NBLV && tiled == TILEDV && far == FARV) {                                     \
+        lm_rows_bf16<NBLV, TILEDV, FARV>                                                     \
+            <<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab);                            \
     } else
+#define WF_ROWS(NBLV)                                                                        \
+    WF_ROWS_AS(NBLV, false, false) WF_ROWS_AS(NBLV, true, false)                             \
+    WF_ROWS_AS(NBLV, false, true) WF_ROWS_AS(NBLV, true, true)
         // Row-major weights in whole lines through LDS; tiled ones too where
         // a wave has at most two blocks and several row groups, too little
         // for its register loads to cover the memory latency (20 rows,
@@ -1071,6 +1088,7 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
             { return WF_ERR_UNSUPPORTED; }
         } else
 #undef WF_ROWS
+#undef WF_ROWS_AS
 #define WF_WIDE(NBLV, MBWV, PV)                                                              \
     if (nbl == NBLV && mbw <= MBWV) {                                                      \
         lm_wide_bf16<NBLV, MBWV, PV><<<f.n_tiles, 512, 0, stream>>>(hb, wb, f, d, vocab);  \
@@ -1086,16 +1104,21 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
         const uint16_t *wb = static_cast<const uint16_t *>(w_lm);
         const int nblk_v = cdiv(vocab, 16);
         const int nbl = cdiv(gamma, 16);
-        const int wf = cdiv(nblk_v, 8) < kLmStreamGrid ? 2 : 4;
+        const bool far = d >= kFarRows;
+        const int wf = far || cdiv(nblk_v, 8) < kLmStreamGrid ? 2 : 4;
         f.n_tiles = cdiv(nblk_v, 2 * wf);
         const dim3 grid(f.n_tiles);
-#define WF_ROWS(NBLV, WFV, WKV, NBUFV)                                                       \
-    if (nbl == NBLV && wf == WFV) {                                                          \
-        lm_gemm_bf16<NBLV, WFV, WKV, NBUFV>                                                  \
+#define WF_ROWS(NBLV, WFV, WKV, NBUFV, FARV)                                                 \
+    if (nbl == NBLV && wf == WFV && far == FARV) {                                           \
+        lm_gemm_bf16<NBLV, WFV, WKV, NBUFV, FARV>                                            \
             <<<grid, 64 * WFV * WKV, 0, stream>>>(hb, wb, f, d, vocab);                      \
     } else
-        WF_ROWS(1, 2, 2, 4) WF_ROWS(2, 2, 2, 4) WF_ROWS(3, 2, 2, 4) WF_ROWS(4, 2, 2, 4)
-        WF_ROWS(1, 4, 1, 3) WF_ROWS(2, 4, 1, 3) WF_ROWS(3, 4, 2, 3) WF_ROWS(4, 4, 2, 3)
+        WF_ROWS(1, 2, 2, 4, false) WF_ROWS(2, 2, 2, 4, false)
+        WF_ROWS(3, 2, 2, 4, false) WF_ROWS(4, 2, 2, 4, false)
+        WF_ROWS(1, 4, 1, 3, false) WF_ROWS(2, 4, 1, 3, false)
+        WF_ROWS(3, 4, 2, 3, false) WF_ROWS(4, 4, 2, 3, false)
+        WF_ROWS(1, 2, 2, 4, true) WF_ROWS(2, 2, 2, 4, true)
+        WF_ROWS(3, 2, 2, 4, true) WF_ROWS(4, 2, 2, 4, true)
         { return WF_ERR_UNSUPPORTED; }
 #undef WF_ROWS
     } else if (dt == WF_BF16) {

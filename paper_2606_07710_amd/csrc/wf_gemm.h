@@ -36,8 +36,9 @@ struct GemmBlock {
 
 // NT: W with the non-temporal hint (each workgroup the only reader of its
 // W rows; the whole-line copies ask for each line once).
-// FAR: any input dimension.  Else a block's offsets are 32-bit, for input
-// dimensions below 2^26.
+// FAR: offsets of 64 bits per lane, for any input dimension.  Else a lane's
+// offset within eight rows is 32-bit, and so is the byte offset along the input
+// dimension: for dimensions below 2^28, tiled sources below 2^26.
 template <int FB, int NB, int WF, int WT, int WK, int NBUF, bool NT, bool FAR = false>
 struct TileGemm {
     using Off = std::conditional_t<FAR, long long, int>;
@@ -95,8 +96,9 @@ struct TileGemm {
             } else {
                 const int r = 8 * hf + lane / 8;             // row of the block
                 const int g = (lane & 7) ^ ((r >> 1) & 7);   // granule of the row's line
-                base[i] = b.p;
-                voff[i] = min(r, b.rows - 1) * ld + (one_half ? g & 3 : g) * 16;
+                const int r0 = min(8 * hf, b.rows - 1);
+                base[i] = b.p + r0 * ld;
+                voff[i] = (min(r, b.rows - 1) - r0) * ld + (one_half ? g & 3 : g) * 16;
                 step_bytes[i] = kGemmStep * 2;
                 last_off[i] = (Off)max(d_in - kGemmStep, 0) * 2;
             }

@@ -77,6 +77,10 @@ def test_masked_and_infinite_logits(gamma, d):
     (64, (1 << 25) + (1 << 22), 20, False),     # 64 rows of h span more than 4 GB
     (64, (1 << 25) + (1 << 22), 20, True),
     (2, 150000000, 16, False),                  # a 16-row block of W does
+    (2, 150000000, 5, False),
+    (17, 320000000, 16, False),                 # eight rows do
+    (17, 320000000, 16, True),
+    (9, 320000032, 14, False),
 ])
 def test_rows_more_than_4gb_apart(gamma, d, vocab, tiled):
     """Byte offsets past 32 bits, with inputs that are zero but for a few
