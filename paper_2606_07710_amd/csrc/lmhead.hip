@@ -627,7 +627,7 @@ __global__ __launch_bounds__(64 * WF * WK) void lm_gemm_bf16(const uint16_t *__r
 // than the tiled form's.)
 // FAR: a lane's offset within eight rows takes 64 bits (d >= kFarRows);
 // shorter rows keep it to 32 beside a wave-uniform base (61 rows, d 2560:
-// 150.3 us per call, with 64 bits 151.0 to 151.7).
+// 150.7 us per call, with 64 bits 151.0 to 151.7).
 constexpr int kRowsBuf = 6;
 constexpr int kFarRows = 1 << 28;
 
@@ -802,14 +802,14 @@ __global__ __launch_bounds__(512) void lm_rows_bf16(const uint16_t *__restrict__
     }
 }
 
-// fp32 LM head for up to 16 verify rows: workgroup t owns the 64-row vocabulary tile t, each of its 8
-// waves eight of the rows; a wave's lanes run along the hidden dimension, so W
-// and h are read in whole lines straight into registers, and the 64 sums of eight
-// verify rows by eight vocabulary rows meet in a halving reduction over the
-// lanes (sum v ends in lane v).  More than eight verify rows take a second
-// pass over the tile.  VEC floats a
-// load: 4 where rows are a multiple of 4 long (the entry points take 16-byte
-// aligned tensors only, so rows are aligned too), else 1.
+// fp32 LM head for up to 16 verify rows: workgroup t owns the 64-row
+// vocabulary tile t, each of its 8 waves eight of the rows; a wave's lanes run
+// along the hidden dimension, so W and h are read in whole lines straight into
+// registers, and the 64 sums of eight verify rows by eight vocabulary rows meet
+// in a halving reduction over the lanes (sum v ends in lane v).  More than
+// eight verify rows take a second pass over the tile.  VEC floats a load: 4
+// where rows are a multiple of 4 long (the entry points take 16-byte aligned
+// tensors only, so rows are aligned too), else 1.
 //
 // What bounds it at the sizes it is used for (8 rows, d 512, vocabulary 4096:
 // 8 MB) is memory latency with 64 workgroups on the chip: every load of a
@@ -1098,8 +1098,12 @@ wf_status_t launch_lmhead(wf_dtype_t dt, const void *h, const void *w_lm,
 #undef WF_WIDE
     } else if (dt == WF_BF16 && !tiled) {
         // 128-row tiles, with three or four token blocks in two k groups (61
-        // rows, d 2880: 161.6 against 162.9 us); 64-row tiles where 128-row ones would not give every CU a
-        // workgroup (20 rows, vocabulary 32000, d 2560: 37.0 against 38.1)
+        // rows, d 2880: 161.6 against 162.9 us); 64-row tiles where 128-row
+        // ones would not give every CU a workgroup (20 rows, vocabulary 32000,
+        // d 2560: 37.0 against 38.1).  Small vocabularies too: one workgroup
+        // per 64 rows with d split over eight waves, which this replaces, took
+        // 23.2 us at vocabulary 500, d 2880, one row (18.4 now), 43.7 at 61
+        // rows (24.1)
         const uint16_t *hb = static_cast<const uint16_t *>(h);
         const uint16_t *wb = static_cast<const uint16_t *>(w_lm);
         const int nblk_v = cdiv(vocab, 16);

@@ -255,7 +255,7 @@ bool pick_tile(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers, 
 bool prefill_gemm_takes(int n_tok, int d_in, int n_kv_heads, int head_dim, int n_layers,
                         bool w_tiled) {
     GemmTile t;
-    // (offsets within a 16-row block are 32-bit)
+    // (byte offsets along the input dimension are 32-bit, tiled: 32 bytes a dim)
     return 32LL * d_in < (1LL << 31) &&
            pick_tile(n_tok, d_in, n_kv_heads, head_dim, n_layers, w_tiled, t);
 }
