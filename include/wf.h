@@ -243,11 +243,11 @@ wf_status_t wf_verify_attn_tree(wf_dtype_t dt, const void *q,
  *           start_pos + n_tok <= cap; head_dim in {64, 128};
  *           d_in >= 1, and d_in % 32 == 0 for the bf16 dtypes.
  * workspace >= wf_kv_only_prefill_workspace_bytes(...) bytes (may be NULL
- *           when that is 0: fp32, or no tokens).  With few tokens the bf16
- *           path splits the input dimension across a power-of-two number of
- *           workgroups whose sums meet up a fixed binary tree
- *           (deterministic), using exchange slots in the workspace's zero
- *           block.
+ *           when that is 0: fp32, or no tokens).  With few tokens, or few
+ *           heads over long inputs, the bf16 path splits the input dimension
+ *           across a power-of-two number of workgroups whose sums meet up a
+ *           fixed binary tree (deterministic), using exchange slots in the
+ *           workspace's zero block.
  * ---------------------------------------------------------------------- */
 wf_status_t wf_kv_only_prefill(wf_dtype_t dt, const void *x, const void *w_k,
                                const void *w_v, void *k_cache, void *v_cache,

@@ -17,9 +17,10 @@
 // cache pair.  Tokens are the MFMA N dimension (blocks of 16).
 // RoPE angles are formed in fp64: at positions ~65K an fp32 angle would be
 // off by ~4e-3 rad.
-// Calls with many tokens, or many layers, run prefill_gemm.hip instead: this
-// kernel re-reads the activations for every 32 or 64 features and the
-// weights for every 64 tokens.
+// Calls with many tokens, or many layers, run prefill_gemm.hip instead, unless
+// few heads and a long input dimension leave its chains the longer (the rule
+// stands there): this kernel re-reads the activations for every 32 or 64
+// features and the weights for every 64 tokens.
 #include <cmath>
 
 #include "wf_api_internal.h"
